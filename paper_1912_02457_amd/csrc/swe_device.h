@@ -51,7 +51,8 @@ struct Ctrl {
     // dt update policy (Dom::dt_interval > 0): dt held since the last update
     // and the time of the next update, per parity like t
     double dt_hold[2], t_upd[2];
-    double pad[5];
+    double dt_step;      // dt of the step in progress, published by stage 1 for stage 2
+    double pad[4];
     // max over non-land cells of max((|u|+c)/dx, (|v|+c)/dy) as float bits, per parity
     uint32_t wslot[2][kCflSlots][kCflStride];
 };
@@ -88,6 +89,7 @@ struct Dom {
     float dx, dy, rdx, rdy, kx, ky; // kx = dx / (2 g)
     float g, theta, kappa, inv2kappa, kappa_sq, courant_q; // courant_q = C / 4
     float theta2;                  // 2 theta (the limiter works on twice the slopes)
+    float deep;                    // water deeper than this needs no wet-dry treatment (deep_water)
     float grdx2, grdy2;            // g / (2 dx), g / (2 dy): the bathymetry source's factors
     int friction;
     float fric_c;                  // r, r, or g n^2 (Manning)
@@ -121,13 +123,24 @@ struct Dom {
     double *partials;              // diagnostics partial sums
 };
 
+// Depth above which the stage kernels skip the wet-dry treatment of a row of
+// water.  2 kappa: there h* = h exactly (eq. desing_ours takes h itself from
+// kappa on, and the other branch has rounded clear of it).  1/64 m: a margin
+// of many ulps of any surface elevation on Earth (one ulp of 8192 m is 1 mm),
+// so that a face value that clears it is never touched by the wet-dry fix.
+inline float deep_water(double kappa) { return (float)(2.0 * kappa > 0.015625 ? 2.0 * kappa : 0.015625); }
+
 // frame layout (see the top of this file)
+// (templates: the device code also reads a Dom through the constant address
+// space)
 constexpr int kFrame = kHalo;
-__host__ __device__ inline uint32_t cell_off(const Dom &d, int r, int i)
+template <class D>
+__host__ __device__ inline uint32_t cell_off(const D &d, int r, int i)
 {
     return (uint32_t)(r + kFrame) * (uint32_t)d.pitch + (uint32_t)(i + kFrame);
 }
-__host__ __device__ inline uint32_t corner_off(const Dom &d, int r, int i)
+template <class D>
+__host__ __device__ inline uint32_t corner_off(const D &d, int r, int i)
 {
     return (uint32_t)(r + kFrame) * (uint32_t)d.cpitch + (uint32_t)(i + kFrame);
 }
@@ -234,7 +247,8 @@ __host__ __device__ inline int block_tile(const Tiling &T, int b, int wid)
 // Strip and rows [y0, y1) of a tile (0 <= tile < T.ntiles).  Within the head
 // and within the tail, tiles are numbered strip-major (order bit 0 clear) or
 // row-band-major, with the strips in the order 0, last, 1, 2, ...
-__host__ __device__ inline void tile_place(const Tiling &T, int tile, int ny, int &strip, int &y0, int &y1)
+template <class T_>
+__host__ __device__ inline void tile_place(const T_ &T, int tile, int ny, int &strip, int &y0, int &y1)
 {
     int t = tile, nb = T.nrb1, by = T.by, base = 0;
     if (tile >= T.ntiles1) {

@@ -66,11 +66,11 @@ __device__ __forceinline__ uint32_t local_off(uint32_t v)
 // bfloat16.  An error is at most half an ulp of its value, so the pair keeps
 // the value to about 2^-10 of a float32 ulp.  A load takes two more bits of
 // address arithmetic and one shift; a store one add.
-__device__ __forceinline__ float ld_lo(const uint16_t *__restrict__ base, uint32_t off)
+__device__ __forceinline__ uint32_t ld_lo(const uint16_t *__restrict__ base, uint32_t off)
 {
-    const uint32_t b = *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(base) + (off << 1));
-    return __uint_as_float(b << 16);
+    return *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(base) + (off << 1));
 }
+__device__ __forceinline__ float lo_value(uint32_t bits) { return __uint_as_float(bits << 16); }
 __device__ __forceinline__ void st_lo(uint16_t *__restrict__ base, uint32_t off, float v)
 {
     *reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(base) + (off << 1)) =
@@ -88,9 +88,11 @@ __device__ __forceinline__ float two_sum(float a, float b, float &err)
 constexpr uint32_t kSign = 0x80000000u;
 __device__ __forceinline__ float flip_sign(float x, uint32_t s) { return __uint_as_float(__float_as_uint(x) ^ s); }
 
-// rounding errors of the own cell's stored Q^n (0) and Q* (1) values
+// rounding errors of the own cell's stored Q^n (0) and Q* (1) values, as
+// stored: the shift to a float comes where they are used (next to the load it
+// would wait for it)
 struct Lo {
-    float e0, u0, v0, e1, u1, v1;
+    uint32_t e0, u0, v0, e1, u1, v1;
 };
 
 // Value held by lane-1 / lane+1 through a whole-wave DPP shift (wave_shr:1
@@ -105,11 +107,22 @@ __device__ __forceinline__ int from_right(int v) { return __builtin_amdgcn_updat
 __device__ __forceinline__ float from_left(float v) { return __int_as_float(from_left(__float_as_int(v))); }
 __device__ __forceinline__ float from_right(float v) { return __int_as_float(from_right(__float_as_int(v))); }
 
+// A wave-uniform lane mask as a per-lane condition (no vector instruction),
+// and the mask of the lanes whose left / right neighbour is in a mask.
+__device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+// Uniform conditions of the row loop, the usual case in line: the other one's
+// code moves out of the loop's way (and out of its instruction cache lines).
+__device__ __forceinline__ bool likely(bool c) { return __builtin_expect(c, 1); }
+__device__ __forceinline__ bool unlikely(bool c) { return __builtin_expect(c, 0); }
+__device__ __forceinline__ uint64_t left_in(uint64_t m) { return m << 1; }
+__device__ __forceinline__ uint64_t right_in(uint64_t m) { return m >> 1; }
+
 // eq. desing_ours; h^2/(2 kappa) + kappa/2 is formed as (h h + kappa^2) /
 // (2 kappa), one uniform operand per instruction.  That value q is never
 // below |h| (equal only at |h| = kappa) and is below kappa exactly when |h|
 // is, so max(|h|, min(q, kappa)) is the median of |h|, q and kappa.
-__device__ __forceinline__ float desing(float h, const Dom &d)
+template <class D>
+__device__ __forceinline__ float desing(float h, const D &d)
 {
     const float q = fmaf(h, h, d.kappa_sq) * d.inv2kappa;
     const float m = __builtin_amdgcn_fmed3f(fabsf(h), q, d.kappa);
@@ -121,13 +134,13 @@ __device__ __forceinline__ float desing(float h, const Dom &d)
 // differences dm, dp: minmod(2 theta dm, dm + dp, 2 theta dp), given as its
 // three candidates a = 2 theta dm, b = dm + dp, c = 2 theta dp (scaling by
 // two is exact, so callers take a quarter of it where the slope's half is
-// used, bitwise the same as halving the minmod).  minmod of three numbers
-// is the median of (their minimum, 0, their maximum): the minimum if all
-// are positive, the maximum if all are negative, else 0.  Along y each
-// row's 2 theta multiple serves the faces below and above it.
+// used, bitwise the same as halving the minmod).  The median of two numbers
+// and 0 is the smaller one in magnitude if they agree in sign, else 0; b has
+// the common sign of a and c, so two medians give the minmod of all three.
+// Along y each row's 2 theta multiple serves the faces below and above it.
 __device__ __forceinline__ float limited2(float a, float b, float c)
 {
-    return __builtin_amdgcn_fmed3f(fminf(a, fminf(b, c)), 0.f, fmaxf(a, fmaxf(b, c)));
+    return __builtin_amdgcn_fmed3f(__builtin_amdgcn_fmed3f(a, c, 0.f), b, 0.f);
 }
 
 // limited2 along x, the forward difference being the right neighbour's
@@ -196,7 +209,8 @@ __device__ __forceinline__ uint32_t read_wmax(const Ctrl *c, int parity, int lan
 }
 
 
-__device__ __forceinline__ void wind_at(const Dom &d, double tau, float &wx, float &wy)
+template <class D>
+__device__ __forceinline__ void wind_at(const D &d, double tau, float &wx, float &wy)
 {
     if (d.nw <= 0) { wx = wy = 0.f; return; }
     int k; double s;
@@ -212,6 +226,25 @@ __device__ __forceinline__ void wind_at(const Dom &d, double tau, float &wx, flo
 
 
 
+// A domain block read through the scalar cache where it is used: in the rare
+// parts of a tile (frame copies, relaxation zone, boundary tables) the fields
+// come from here, so that they hold no scalar registers over the row loop
+// (beyond the 102 there are, every use of a spilled one costs a vector
+// instruction).  The empty asm keeps the loads from moving out of the loop.
+using DomK = const __attribute__((address_space(4))) Dom;
+__device__ __forceinline__ DomK &cold(DomK *p)
+{
+    asm volatile("" : "+s"(p));
+    return *p;
+}
+// A uniform value whose tests stay where they are written: a test moved out
+// of the row loop becomes a 64-bit lane mask, two more scalar registers.
+__device__ __forceinline__ int here(int v)
+{
+    asm volatile("" : "+s"(v));
+    return v;
+}
+
 struct F3 { float e, p, q; };
 
 // eq. numerical_flux for a face with depth Hf between a left state (eL,pL,qL)
@@ -223,13 +256,15 @@ struct F3 { float e, p, q; };
 // alpha = 1/2, gamma = 0 give the average of the two physical fluxes.  No
 // branches, so the flux of a face can be interleaved with other work.
 // The pressure uses the perturbation form (see the file header).
+template <class D>
 __device__ __forceinline__ F3 cu_flux(float eL, float pL0, float qL0, float eR, float pR0, float qR0,
-                                      float Hf, const Dom &d)
+                                      float Hf, const D &d)
 {
     float hL = eL + Hf, hR = eR + Hf;
     float rL = rcp(desing(hL, d)), rR = rcp(desing(hR, d));
     float uL = pL0 * rL, vL = qL0 * rL, uR = pR0 * rR, vR = qR0 * rR;
-    float pL = hL * uL, pR = hR * uR;
+    // h* = h where the water is deep: the face momentum is h u = p itself
+    float pL = hL > d.deep ? pL0 : hL * uL, pR = hR > d.deep ? pR0 : hR * uR;
     float cL = fsqrt(d.g * fmaxf(hL, 0.f)), cR = fsqrt(d.g * fmaxf(hR, 0.f));
     float ap = fmaxf(fmaxf(uL + cL, uR + cR), 0.f);
     float am = fminf(fminf(uL - cL, uR - cR), 0.f);
@@ -258,22 +293,59 @@ __device__ __forceinline__ F3 cu_flux(float eL, float pL0, float qL0, float eR, 
     return r;
 }
 
-// face with the land rule: a face touching land carries the reflective-wall
-// flux of its wet side; a face between two land cells carries nothing.
-// `anyland` is uniform over the wave (some lane of the rows involved is
-// land); without it the land selects are skipped, which gives bitwise the
-// same flux.
-__device__ __forceinline__ F3 face_flux(float eL, float pL, float qL, float eR, float pR, float qR,
-                                        bool lL, bool lR, bool anyland, float Hf, const Dom &d)
+// The same flux, bit for bit (up to the sign of a zero), where the face
+// depth and the water depth on both sides exceed Dom::deep: h* = h, the face
+// is below the datum (min(H_f,0) = 0) and a+ - a- >= 2 sqrt(g h) > 0, so the
+// desingularisation, the dry-face weights and the datum terms drop out: 38
+// instead of 66 vector instructions, beside the five transcendental ones.
+template <class D>
+__device__ __forceinline__ F3 cu_flux_deep(float eL, float pL, float qL, float eR, float pR, float qR, float Hf,
+                                           const D &d)
 {
-    if (anyland) {
+    const float hL = eL + Hf, hR = eR + Hf;
+    const float rL = rcp(hL), rR = rcp(hR);
+    const float uL = pL * rL, vL = qL * rL, uR = pR * rR, vR = qR * rR;
+    const float cL = fsqrt(d.g * hL), cR = fsqrt(d.g * hR);
+    const float ap = fmaxf(fmaxf(uL + cL, uR + cR), 0.f);
+    const float am = fminf(fminf(uL - cL, uR - cR), 0.f);
+    const float H2 = Hf + Hf;
+    const float PL = 0.5f * d.g * eL * (eL + H2), PR = 0.5f * d.g * eR * (eR + H2);
+    const float FL = fmaf(pL, uL, PL), FR = fmaf(pR, uR, PR);
+    const float al = ap * rcp(ap - am);
+    const float ga = am * al;
+    const float dp = pL - pR;
+    F3 r;
+    r.e = fmaf(al, dp, fmaf(ga, eR - eL, pR));
+    r.p = fmaf(al, FL - FR, fmaf(ga, -dp, FR));
+    r.q = r.e * (r.e >= 0.f ? vL : vR);
+    return r;
+}
+
+// What a row of faces has beside plain deep water, uniform over the wave:
+// DEEP: every face that touches water is deep in the sense of cu_flux_deep;
+// LAND: some cell is land.  The kernels decide once per row and then run
+// straight-line code for both directions: decided at every use (twenty
+// branches a row instead of seven), stage 2 took 7 % longer where two waves
+// share a SIMD (2600 x 900 coast in 24-row bands: 56.0 against 52.4 us) and 4 %
+// where they fill it (2048 x 2048 in 12-row bands: 41.0 against 39.4).
+//
+// Face with the land rule: a face touching land carries the reflective-wall
+// flux of its wet side; a face between two land cells carries nothing.  landL
+// and landR are the lanes whose left (lower) and right (upper) cell is land;
+// without any the selects leave every value as it is.
+template <bool DEEP, bool LAND, class D>
+__device__ __forceinline__ F3 face_flux(float eL, float pL, float qL, float eR, float pR, float qR,
+                                        uint64_t landL, uint64_t landR, float Hf, const D &d)
+{
+    if (LAND) {
+        const bool lL = in_mask(landL), lR = in_mask(landR);
         const float e2R = lR ? eL : eR, p2R = lR ? -pL : pR, q2R = lR ? qL : qR;
         const float e2L = lL ? eR : eL, p2L = lL ? -pR : pL, q2L = lL ? qR : qL;
         eL = e2L; pL = p2L; qL = q2L;
         eR = e2R; pR = p2R; qR = q2R;
     }
-    F3 r = cu_flux(eL, pL, qL, eR, pR, qR, Hf, d);
-    if (anyland && lL && lR) r.e = r.p = r.q = 0.f;
+    F3 r = DEEP ? cu_flux_deep(eL, pL, qL, eR, pR, qR, Hf, d) : cu_flux(eL, pL, qL, eR, pR, qR, Hf, d);
+    if (LAND && in_mask(landL & landR)) r.e = r.p = r.q = 0.f;
     return r;
 }
 
@@ -283,8 +355,11 @@ __device__ __forceinline__ F3 face_flux(float eL, float pL, float qL, float eR, 
 //   (eta^E + eta^W)(H_E - H_W) + min(H_E,0)^2 - min(H_W,0)^2,
 // one formula for wet and dry faces with no cancellation of large terms;
 // the caller scales it by g / (2 dx) or g / (2 dy).
+// Below the datum (DEEP) the last two terms are zero.
+template <bool DEEP>
 __device__ __forceinline__ float bathy_source(float eE, float eW, float HE, float HW)
 {
+    if (DEEP) return (eE + eW) * (HE - HW);
     float mE = fminf(HE, 0.f), mW = fminf(HW, 0.f);
     float dry = fmaf(mE, mE, -(mW * mW));
     return fmaf(eE + eW, HE - HW, dry);
@@ -292,19 +367,19 @@ __device__ __forceinline__ float bathy_source(float eE, float eW, float HE, floa
 
 // bed shear stress coefficient S >= 0, the source being -S (hu, hv), from the
 // cell's reciprocal desingularised depth ri = 1/h*
-__device__ __forceinline__ float friction_coeff(const Dom &d, float ri, float hu, float hv)
+template <class D>
+__device__ __forceinline__ float friction_coeff(int law, const D &d, float ri, float hu, float hv)
 {
-    if (d.friction == FR_NONE) return 0.f;
-    float ra = fabsf(ri);
-    if (d.friction == FR_LINEAR) return d.fric_c * ra;
-    float speed = fsqrt(hu * hu + hv * hv) * ra;
-    if (d.friction == FR_QUADRATIC) return d.fric_c * speed * ra * ra;
+    const float ra = fabsf(ri), coeff = d.fric_c;
+    if (law <= FR_LINEAR) return law == FR_NONE ? 0.f : coeff * ra;
+    const float speed = fsqrt(hu * hu + hv * hv) * ra;
+    if (law == FR_QUADRATIC) return coeff * speed * ra * ra;
     // Manning: g n^2 |u| / a^(4/3) = g n^2 |u| ra^(4/3)
-    float ra43 = __builtin_amdgcn_exp2f((4.0f / 3.0f) * __builtin_amdgcn_logf(ra));
-    return d.fric_c * speed * ra43;
+    const float ra43 = __builtin_amdgcn_exp2f((4.0f / 3.0f) * __builtin_amdgcn_logf(ra));
+    return coeff * speed * ra43;
 }
 
-// Face values eta +/- rho of a cell with the wet-dry fix of eq. KxE_adjust:
+// Wet-dry fix of eq. KxE_adjust of a cell's face values ep, em = eta +/- rho:
 // a face value below the bottom (eta_f + H_f < 0) is set to the bottom and
 // the other face takes 2 eta - eta_f, keeping the cell average; first the
 // face on the + side, then the one on the - side.  As max/min: raising
@@ -312,10 +387,8 @@ __device__ __forceinline__ float friction_coeff(const Dom &d, float ri, float hu
 // min of itself and 2 eta + H_+ -- exact when the fix applies, and equal
 // to the unfixed value otherwise (up to one rounding when the two are
 // within an ulp).
-__device__ __forceinline__ void positivity_fix(float e, float rho, float Hp, float Hm, float &ep, float &em)
+__device__ __forceinline__ void positivity_fix(float e, float Hp, float Hm, float &ep, float &em)
 {
-    ep = e + rho;
-    em = e - rho;
     ep = fmaxf(ep, -Hp);
     em = fminf(em, fmaf(2.f, e, Hp));
     em = fmaxf(em, -Hm);
@@ -328,8 +401,10 @@ struct Row {
     float cx, cy;          // Coriolis terms of the reconstruction (f v, -f u)
     float Hw, He, Hs, Hn, Hb;
     float ri;              // 1 / h* of the cell
-    int land;
-    bool anyland;          // some lane of the row is land (uniform over the wave)
+    uint64_t land;         // lanes whose cell is land
+    uint64_t shallown;     // lanes whose north-west corner depth is not deep
+    uint64_t shallow;      // water lanes with a face or water depth that is not deep (Dom::deep)
+    uint64_t shallowy;     // output lanes whose water at the north or south face is not deep
     float dmL, dmU, dmV;   // y backward differences (this row minus the row below)
     float tmL, tmU, tmV;   // the same times 2 theta
     float eN, eS, uN, vN;  // north/south face values once the row was the middle row
@@ -338,21 +413,28 @@ struct Row {
 // face depths, mean depth, land flag and Coriolis terms of a row from its
 // four corner depths (south corners cs*, north corners cn*); the south face
 // depth hs is the north face depth of the row below, 0.5 (cs0 + cs1)
-template <bool PROJ>
+template <bool PROJ, class D>
 __device__ __forceinline__ void row_terms(Row &R, float cs0, float cs1, float cn0, float cn1, float hs, float th,
-                                          const Dom &d)
+                                          const D &d)
 {
     R.Hw = 0.5f * (cs0 + cn0);
     R.He = 0.5f * (cs1 + cn1);
     R.Hs = hs;
     R.Hn = 0.5f * (cn0 + cn1);
     R.Hb = 0.25f * ((cs0 + cn0) + (cs1 + cn1));
-    float h = R.e + R.Hb;
-    float ri = rcp(desing(h, d));
+    const float h = R.e + R.Hb;
+    R.land = __builtin_amdgcn_ballot_w64(isnan(R.f));
+    // every face depth is the mean of two corner depths, and a cell's east
+    // corners are the west ones of the next lane (lane 63's are not covered;
+    // no output depends on its faces).  A depth that is not a number counts
+    // as shallow
+    const uint64_t north = __builtin_amdgcn_ballot_w64(!(cn0 > d.deep));
+    const uint64_t corners = north | R.shallow;  // R.shallow: south on entry
+    R.shallow = (corners | right_in(corners) | __builtin_amdgcn_ballot_w64(!(h > d.deep))) & ~R.land;
+    R.shallown = north;
+    const float ri = rcp(desing(h, d));
     R.ri = ri;
     float uu = R.u * ri, vv = R.v * ri;
-    R.land = isnan(R.f) ? 1 : 0;
-    R.anyland = __ballot(R.land) != 0;
     if (PROJ) {
         float c = __cosf(th), s = __sinf(th);
         float ue = c * uu - s * vv, vn = s * uu + c * vv;
@@ -366,7 +448,8 @@ __device__ __forceinline__ void row_terms(Row &R, float cs0, float cs1, float cn
 
 // backward differences along y of row C against the row B below it; the
 // K-type difference of eq. Kbackwards in its y form (L = g(eta + U))
-__device__ __forceinline__ void y_diff(Row &C, const Row &B, const Dom &d)
+template <class D>
+__device__ __forceinline__ void y_diff(Row &C, const Row &B, const D &d)
 {
     C.dmL = C.e - B.e - d.ky * (B.cy + C.cy);
     C.dmU = C.u - B.u;
@@ -376,23 +459,26 @@ __device__ __forceinline__ void y_diff(Row &C, const Row &B, const Dom &d)
     C.tmV = d.theta2 * C.dmV;
 }
 
-// limited y-slopes and N/S face values of row B (eq. hE in its N/S form with
-// the wet-dry fix of eq. KxE_adjust); stores the N values and eS in B and
-// returns the S momenta for the face below B
-__device__ __forceinline__ void y_faces(Row &B, const Row &C, int landA, bool anylandA, const Dom &d, float &uS,
+// limited y-slopes and N/S face values of row B (eq. hE in its N/S form);
+// stores the N values, eS and the lanes that need the wet-dry fix in B and
+// returns the S momenta for the face below B.  out: the output lanes of the
+// tile, the only ones whose y-fluxes are used.
+template <class D>
+__device__ __forceinline__ void y_faces(Row &B, const Row &C, uint64_t landA, uint64_t out, const D &d, float &uS,
                                         float &vS)
 {
     // twice the limited slopes (limited2)
     float sL = limited2(B.tmL, B.dmL + C.dmL, C.tmL);
     float sU = limited2(B.tmU, B.dmU + C.dmU, C.tmU);
     float sV = limited2(B.tmV, B.dmV + C.dmV, C.tmV);
-    // first order next to land (skipped for rows without land nearby)
-    if ((anylandA || C.anyland) && (landA || C.land)) sL = sU = sV = 0.f;
-    float rho = 0.25f * sL + d.ky * B.cy;
-    float eN, eS;
-    positivity_fix(B.e, rho, B.Hn, B.Hs, eN, eS);
-    B.eN = eN;
-    B.eS = eS;
+    // first order next to land
+    if (in_mask(landA | C.land)) sL = sU = sV = 0.f;
+    const float rho = 0.25f * sL + d.ky * B.cy;
+    B.eN = B.e + rho;
+    B.eS = B.e - rho;
+    // lanes of deep water at both faces: the wet-dry fix leaves them as they are
+    const float low = fminf(B.eN + B.Hn, B.eS + B.Hs);
+    B.shallowy = (B.shallow | (__builtin_amdgcn_ballot_w64(!(low > d.deep)) & ~B.land)) & out;
     B.uN = B.u + 0.25f * sU;
     B.vN = B.v + 0.25f * sV;
     uS = B.u - 0.25f * sU;
@@ -401,20 +487,25 @@ __device__ __forceinline__ void y_faces(Row &B, const Row &C, int landA, bool an
 
 // flux through the face between row A (below, its N values) and row B
 // (above, its S values): normal momentum hv, transverse hu
-__device__ __forceinline__ F3 y_flux(const Row &A, const Row &B, float uS, float vS, const Dom &d)
+template <bool DEEP, bool LAND, class D>
+__device__ __forceinline__ F3 y_flux(const Row &A, const Row &B, float uS, float vS, const D &d)
 {
-    return face_flux(A.eN, A.vN, A.uN, B.eS, vS, uS, A.land != 0, B.land != 0, A.anyland || B.anyland, B.Hs, d);
+    return face_flux<DEEP, LAND>(A.eN, A.vN, A.uN, B.eS, vS, uS, A.land, B.land, B.Hs, d);
 }
 
+enum {
+    kTileEdge = 1,    // writes ghost cells (output cells within two cells of a side)
+    kTileFrs = 2,     // has output cells in a relaxation zone
+    kTileFriction = 2 // shift of the friction law
+};
 struct TileCtx {
     int i, o;        // column of this lane, output row
+    int lane, x0;    // lane and its strip's first output column
     bool out_lane;   // lane owns an output cell
+    uint64_t out;    // the lanes that do
+    uint64_t xneed;  // the lanes whose x-faces an output cell depends on (one more on each side)
     float dt, wx, wy;
-    int bk;          // boundary snapshot interval and weight at the stage time
-    double bs;
-    int fbk;         // the same at the time of the stage that reads this stage's output
-    double fbs;
-    bool edge;       // the tile writes ghost cells (output cells within two cells of a side)
+    int kind;        // what the tile's rows do beside the update: bits below
     int fca, fcb;    // ghost columns that copy this lane's cells (frame_copy_cols)
     int wk;          // wind-field snapshot interval and weight at the stage time
     float ws;
@@ -426,7 +517,8 @@ struct TileCtx {
 // the snapshots around the stage time (eq. windstress_interpol); then the
 // stress of Large and Pond, rho_a/rho_w C_D |W| W with C_D = 1.2e-3 below
 // 11 m/s and (0.49 + 0.065 |W|) 1e-3 above, as the kinematic source.
-__device__ __forceinline__ void w10_stress(const Dom &d, const TileCtx &c, float &sx, float &sy)
+template <class D>
+__device__ __forceinline__ void w10_stress(const D &d, const TileCtx &c, float &sx, float &sy)
 {
     float gx = fminf(fmaxf(((float)c.i + 0.5f) * d.w10sx - 0.5f, 0.f), (float)(d.w10nx - 1));
     float gy = fminf(fmaxf(((float)c.o + 0.5f) * d.w10sy - 0.5f, 0.f), (float)(d.w10ny - 1));
@@ -458,47 +550,68 @@ __device__ __forceinline__ void w10_stress(const Dom &d, const TileCtx &c, float
     sy = k * W[1];
 }
 
-// Flow relaxation (eq. frs) of one output cell: whether it lies in a zone,
-// the nearest nested side within the zone (ties W, E, S, N), its weight
-// alpha = 1 - tanh(d/d0) and the two boundary snapshots around the stage
-// time.  The row loop only tests the zone at the start of a row; the loads
-// are issued where the update uses them (held across the row, they raised
-// the register count of the whole stage-2 kernel to three waves per SIMD).
-struct FrsPre {
-    bool zone;
-    float al;
-    float a[3], b[3];
+// Boundary state around the relaxation zones of a tile at the stage time,
+// interpolated once per tile (once per 64 rows) by the whole wave and kept in
+// LDS: along a west or east side it depends on the row, along a south or north
+// side on the column.  (Loaded row by row where the update uses them, two
+// dependent global loads a row made the zone tiles the last ones of every
+// launch: stage 2 of the 2600 x 900 coast took 37.6 us nested on all sides
+// and 28.8 us with walls.)
+constexpr int kFrsRows = 64;
+struct FrsTable {
+    float x[2][kFrsRows][3];  // W, E: rows row0 .. row0 + 63
+    float y[2][kWave][3];     // S, N: the strip's columns
+    float alpha[kMaxFrs];
+    double bs;                // weight and interval of the boundary snapshots
+    int bk, row0;
 };
 
-__device__ __forceinline__ FrsPre frs_prefetch(const Dom &d, const TileCtx &c)
+__device__ __forceinline__ void wave_fence()
 {
-    FrsPre f;
-    const int nx = d.nx, ny = d.ny, i = c.i, o = c.o;
-    // boundary-table entries on the four sides (frs_candidates in swe_maps.h)
-    int idxs[4] = {o, ny + o, 2 * ny + i, 2 * ny + nx + i};
-    int best, dd;
-    frs_side(d, i, o, best, dd);
-    f.zone = c.out_lane && best >= 0 && dd < d.frs_w;
-    f.al = 0.f;
-    f.a[0] = f.a[1] = f.a[2] = f.b[0] = f.b[1] = f.b[2] = 0.f;
-    if (f.zone) {
-        int idx = best == 0 ? idxs[0] : best == 1 ? idxs[1] : best == 2 ? idxs[2] : idxs[3];
-        f.al = d.frs_alpha[dd];
-        const uint32_t P = (uint32_t)d.P;
-        const float *pa = d.bnd + (uint32_t)c.bk * 3u * P + (uint32_t)idx;
-        const float *pb = d.nb > 1 ? pa + 3u * P : pa;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            f.a[q] = pa[q * P];
-            f.b[q] = pb[q * P];
-        }
-    }
-    return f;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// x-direction reconstruction and flux of the output row A, the update of
-// eq. rk2_semiimp and (stage 2) the flow relaxation and CFL reduction.
-// Every lane takes part in the cross-lane exchanges; only output lanes store.
+// external (eta, hu, hv) at perimeter entry idx
+__device__ __forceinline__ void boundary_state(DomK &d, int bk, double t, int idx, float (&q)[3])
+{
+    const uint32_t P = (uint32_t)d.P;
+    const float *pa = d.bnd + (uint32_t)bk * 3u * P + (uint32_t)idx;
+    const float *pb = d.nb > 1 ? pa + 3u * P : pa;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) q[k] = (float)((1.0 - t) * (double)pa[k * P] + t * (double)pb[k * P]);
+}
+
+// rows row0 .. of the west and east tables (tiles are within a zone of those
+// sides or not as a whole strip); by all lanes of one wave
+__device__ __forceinline__ void frs_fill_rows(DomK &d, FrsTable &f, int x0, int row0, int lane)
+{
+    const int y = row0 + lane;
+    if (y < d.ny) {
+        if (d.bc[0] == BC_NESTED && x0 < d.frs_w) boundary_state(d, f.bk, f.bs, y, f.x[0][lane]);
+        if (d.bc[1] == BC_NESTED && x0 + kStrip > d.nx - d.frs_w) boundary_state(d, f.bk, f.bs, d.ny + y, f.x[1][lane]);
+    }
+    if (lane == 0) f.row0 = row0;
+}
+
+// the whole table of a tile that starts at row y0
+__device__ __forceinline__ void frs_fill(DomK &d, FrsTable &f, double tau, int x0, int y0, int y1, int i, int lane)
+{
+    int bk;
+    double bs;
+    time_weights(d.nb, d.bnd_t, tau, bk, bs);
+    if (lane == 0) { f.bk = bk; f.bs = bs; }
+    if (lane < kMaxFrs) f.alpha[lane] = d.frs_alpha[lane];
+    if (i >= 0 && i < d.nx) {
+        if (d.bc[2] == BC_NESTED && y0 < d.frs_w) boundary_state(d, bk, bs, 2 * d.ny + i, f.y[0][lane]);
+        if (d.bc[3] == BC_NESTED && y1 > d.ny - d.frs_w) boundary_state(d, bk, bs, 2 * d.ny + d.nx + i, f.y[1][lane]);
+    }
+    wave_fence();
+    frs_fill_rows(d, f, x0, y0, lane);
+    wave_fence();
+}
+
 // Ghost cells of the state this stage writes (Q* in stage 1, Q^{n+1} in
 // stage 2) for the stage that reads it next, by edge tiles: the wall and
 // periodic copies of a water cell's new values (frame_copy_cols / _rows;
@@ -506,7 +619,7 @@ __device__ __forceinline__ FrsPre frs_prefetch(const Dom &d, const TileCtx &c)
 // uniform), stored from the registers that hold them.  A land cell keeps
 // its state, and its ghosts their values.
 template <int STAGE>
-__device__ __forceinline__ void write_frame_copies(const Dom &d, const TileCtx &c, float e, float u, float v)
+__device__ __forceinline__ void write_frame_copies(DomK &d, const TileCtx &c, float e, float u, float v)
 {
     float *__restrict__ E = STAGE == 1 ? d.eta1 : d.eta;
     float *__restrict__ U = STAGE == 1 ? d.hu1 : d.hu;
@@ -526,46 +639,39 @@ __device__ __forceinline__ void write_frame_copies(const Dom &d, const TileCtx &
 }
 
 // Nested ghosts take the boundary data at the reading stage's time (the
-// interpolation of the boundary loads), independent of the state: written
-// after the row loop by the tiles next to a nested side, four rows at a
-// time so that their loads overlap.
+// interpolation of the boundary loads), independent of the state: written by
+// the tiles next to a nested side, the rows of a west or east side side by
+// side over the lanes.
 template <int STAGE>
-__device__ __forceinline__ void write_frame_nested(const Dom &d, const TileCtx &c, int y0, int y1)
+__device__ __forceinline__ void write_frame_nested(DomK &d, double tau, int x0, int y0, int y1, int lane)
 {
     float *__restrict__ E = STAGE == 1 ? d.eta1 : d.eta;
     float *__restrict__ U = STAGE == 1 ? d.hu1 : d.hu;
     float *__restrict__ V = STAGE == 1 ? d.hv1 : d.hv;
-    const int nx = d.nx, ny = d.ny, x = c.i;
-    const uint32_t P = (uint32_t)d.P;
-    const float *__restrict__ ba = d.bnd + (uint32_t)c.fbk * 3u * P;
-    const float *__restrict__ bb = d.nb > 1 ? ba + 3u * P : ba;
-    const double t = c.fbs;
+    const int nx = d.nx, ny = d.ny;
+    int bk;
+    double t;
+    time_weights(d.nb, d.bnd_t, tau, bk, t);
     auto put = [&](int idx, int xa, int ya, int xb, int yb) {
-        const float e = (float)((1.0 - t) * (double)ba[idx] + t * (double)bb[idx]);
-        const float u = (float)((1.0 - t) * (double)ba[P + idx] + t * (double)bb[P + idx]);
-        const float v = (float)((1.0 - t) * (double)ba[2u * P + idx] + t * (double)bb[2u * P + idx]);
+        float q[3];
+        boundary_state(d, bk, t, idx, q);
         const uint32_t oa = cell_off(d, ya, xa), ob = cell_off(d, yb, xb);
-        st(E, oa, e); st(U, oa, u); st(V, oa, v);
-        st(E, ob, e); st(U, ob, u); st(V, ob, v);
+        st(E, oa, q[0]); st(U, oa, q[1]); st(V, oa, q[2]);
+        st(E, ob, q[0]); st(U, ob, q[1]); st(V, ob, q[2]);
     };
-    // west / east: the lane of column 0 / nx-1, every row of the tile
-    const bool w = d.bc[0] == BC_NESTED && x == 0 && c.out_lane;
-    const bool e = d.bc[1] == BC_NESTED && x == nx - 1 && c.out_lane;
-    if (__ballot(w || e) != 0) {
-        for (int y = y0; y < y1; y += 4) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int yy = y + k;
-                if (yy < y1) {
-                    if (w) put(yy, -1, yy, -2, yy);
-                    if (e) put(ny + yy, nx, yy, nx + 1, yy);
-                }
-            }
+    const bool w = d.bc[0] == BC_NESTED && x0 == 0;
+    const bool e = d.bc[1] == BC_NESTED && x0 + kStrip >= nx;
+    if (w || e) {
+        for (int y = y0 + lane; y < y1; y += kWave) {
+            if (w) put(y, -1, y, -2, y);
+            if (e) put(ny + y, nx, y, nx + 1, y);
         }
     }
-    // south / north: every output lane of row 0 / ny-1
-    if (d.bc[2] == BC_NESTED && y0 == 0 && c.out_lane) put(2 * ny + x, x, -1, x, -2);
-    if (d.bc[3] == BC_NESTED && y1 == ny && c.out_lane) put(2 * ny + nx + x, x, ny, x, ny + 1);
+    const int x = x0 - kHalo + lane;
+    if (lane >= kHalo && lane < kWave - kHalo && x < nx) {
+        if (d.bc[2] == BC_NESTED && y0 == 0) put(2 * ny + x, x, -1, x, -2);
+        if (d.bc[3] == BC_NESTED && y1 == ny) put(2 * ny + nx + x, x, ny, x, ny + 1);
+    }
 }
 
 // lanes of a wave that stored a non-finite state, or a water depth below
@@ -574,10 +680,14 @@ struct BadLanes {
     uint64_t nonfinite, negative;
 };
 
-template <int STAGE, bool PROJ, bool W10, bool COMP>
-__device__ __forceinline__ void finish_row(const Row &A, const F3 &Gs, const F3 &Gn, const TileCtx &c,
-                                           float e0, float u0, float v0, const FrsPre &fp,
-                                           const Dom &d, float &wmax_loc, BadLanes &bad)
+// limited x-slopes and E/W face values of row A, before the wet-dry fix
+struct XFaces {
+    float eE, eW, uE, uW, vE, vW;
+    uint64_t shallow;  // lanes that need the fix, of those an output cell depends on
+};
+
+template <class D>
+__device__ __forceinline__ XFaces x_faces(const Row &A, const TileCtx &c, const D &d)
 {
     const float th2 = d.theta2;
     float eL = from_left(A.e), cxL = from_left(A.cx);
@@ -588,23 +698,65 @@ __device__ __forceinline__ void finish_row(const Row &A, const F3 &Gs, const F3 
     float sK = limited2_x(dmK, th2);
     float sUx = limited2_x(dmU, th2);
     float sVx = limited2_x(dmV, th2);
-    int landR = 0;
-    if (A.anyland) {  // first order next to land (rows with land only)
-        const int landL = from_left(A.land);
-        landR = from_right(A.land);
-        if (landL || landR) sK = sUx = sVx = 0.f;
-    }
-    float rx = 0.25f * sK + d.kx * A.cx;
-    float eE, eW;
-    positivity_fix(A.e, rx, A.He, A.Hw, eE, eW);
-    float uE = A.u + 0.25f * sUx, uW = A.u - 0.25f * sUx;
-    float vE = A.v + 0.25f * sVx, vW = A.v - 0.25f * sVx;
-    F3 Fe = face_flux(eE, uE, vE, from_right(eW), from_right(uW), from_right(vW), A.land != 0, landR != 0,
-                      A.anyland, A.He, d);
-    float Fwe = from_left(Fe.e), Fwp = from_left(Fe.p), Fwq = from_left(Fe.q);
+    // first order next to land
+    if (in_mask(left_in(A.land) | right_in(A.land))) sK = sUx = sVx = 0.f;
+    const float rx = 0.25f * sK + d.kx * A.cx;
+    XFaces x;
+    x.eE = A.e + rx;
+    x.eW = A.e - rx;
+    const float low = fminf(x.eE + A.He, x.eW + A.Hw);
+    x.shallow = (A.shallow | (__builtin_amdgcn_ballot_w64(!(low > d.deep)) & ~A.land)) & c.xneed;
+    x.uE = A.u + 0.25f * sUx;
+    x.uW = A.u - 0.25f * sUx;
+    x.vE = A.v + 0.25f * sVx;
+    x.vW = A.v - 0.25f * sVx;
+    return x;
+}
+
+// what row A's update takes from its faces: the differences of the x-fluxes
+// (east minus west) and the bathymetry sources of both directions
+struct RowFlux {
+    float dFe, dFp, dFq, bx, by;
+};
+
+template <bool DEEP, bool LAND, class D>
+__device__ __forceinline__ RowFlux x_flux(const Row &A, XFaces &x, const D &d)
+{
+    if (!DEEP) positivity_fix(A.e, A.He, A.Hw, x.eE, x.eW);
+    const F3 F = face_flux<DEEP, LAND>(x.eE, x.uE, x.vE, from_right(x.eW), from_right(x.uW), from_right(x.vW), A.land,
+                                       right_in(A.land), A.He, d);
+    RowFlux r;
+    r.dFe = F.e - from_left(F.e);
+    r.dFp = F.p - from_left(F.p);
+    r.dFq = F.q - from_left(F.q);
+    r.bx = bathy_source<DEEP>(x.eE, x.eW, A.He, A.Hw);
+    r.by = bathy_source<DEEP>(A.eN, A.eS, A.Hn, A.Hs);
+    return r;
+}
+
+// x- and y-fluxes of one step of the row loop: the flux through the north
+// face of row A (its south one is known) and row A's x-part
+template <bool DEEP, bool LAND, class D>
+__device__ __forceinline__ void row_fluxes(const Row &A, Row &B, XFaces &x, float uS, float vS, const D &d, F3 &Gn,
+                                           RowFlux &r)
+{
+    if (!DEEP) positivity_fix(B.e, B.Hn, B.Hs, B.eN, B.eS);
+    Gn = y_flux<DEEP, LAND>(A, B, uS, vS, d);
+    r = x_flux<DEEP, LAND>(A, x, d);
+}
+
+// The update of eq. rk2_semiimp of row A and (stage 2) the flow relaxation
+// and CFL reduction.
+template <int STAGE, bool PROJ, bool W10, bool COMP, class D>
+__device__ __forceinline__ void finish_row(const Row &A, const F3 &Gs, const F3 &Gn, const RowFlux &rf,
+                                           const TileCtx &c, float e0, float u0, float v0, const Lo &lo, DomK *dk,
+                                           const FrsTable &ft,
+                                           const D &d, float &wmax_loc, BadLanes &bad)
+{
     // every lane computes; only output lanes over water store (no early exit,
     // so the x and y work of neighbouring rows can be interleaved)
-    const bool store = c.out_lane && !A.land;
+    const uint64_t stored = c.out & ~A.land;
+    const bool store = in_mask(stored);
 
     float Cx, Cy;
     if (PROJ) {
@@ -624,36 +776,24 @@ __device__ __forceinline__ void finish_row(const Row &A, const F3 &Gs, const F3 
         wx += sx;
         wy += sy;
     }
-    float Me = -(Fe.e - Fwe) * d.rdx - (Gn.e - Gs.e) * d.rdy;
-    float Mu = -(Fe.p - Fwp) * d.rdx - (Gn.q - Gs.q) * d.rdy + bathy_source(eE, eW, A.He, A.Hw) * d.grdx2 +
+    float Me = -rf.dFe * d.rdx - (Gn.e - Gs.e) * d.rdy;
+    float Mu = -rf.dFp * d.rdx - (Gn.q - Gs.q) * d.rdy + rf.bx * d.grdx2 +
                Cx + wx;
-    float Mv = -(Fe.q - Fwq) * d.rdx - (Gn.p - Gs.p) * d.rdy + bathy_source(A.eN, A.eS, A.Hn, A.Hs) * d.grdy2 +
+    float Mv = -rf.dFq * d.rdx - (Gn.p - Gs.p) * d.rdy + rf.by * d.grdy2 +
                Cy + wy;
     const uint32_t oo = cell_off(d, c.o, c.i);
     const float dt = c.dt;
-    float S = friction_coeff(d, A.ri, A.u, A.v);
-    // compensated: the stored rounding errors of the cell, loaded where they
-    // are used (held across the row they would raise the register count)
-    Lo lo{0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (COMP) {
-        lo.e0 = ld_lo(d.eta_lo, oo);
-        lo.u0 = ld_lo(d.hu_lo, oo);
-        lo.v0 = ld_lo(d.hv_lo, oo);
-        if (STAGE == 2) {
-            lo.e1 = ld_lo(d.eta1_lo, oo);
-            lo.u1 = ld_lo(d.hu1_lo, oo);
-            lo.v1 = ld_lo(d.hv1_lo, oo);
-        }
-    }
+    const int kind = here(c.kind);
+    float S = friction_coeff(kind >> kTileFriction, d, A.ri, A.u, A.v);
     if (STAGE == 1) {
         float den = rcp(1.f + dt * S);
         if (COMP) {
             // compensated: the increment of each field, added to the stored
             // value plus its rounding error without losing the new error
             float le, lu, lv;
-            const float en = two_sum(A.e, dt * Me + lo.e0, le);
-            const float un = two_sum(A.u, (dt * Mu - dt * S * A.u) * den + lo.u0, lu);
-            const float vn = two_sum(A.v, (dt * Mv - dt * S * A.v) * den + lo.v0, lv);
+            const float en = two_sum(A.e, dt * Me + lo_value(lo.e0), le);
+            const float un = two_sum(A.u, (dt * Mu - dt * S * A.u) * den + lo_value(lo.u0), lu);
+            const float vn = two_sum(A.v, (dt * Mv - dt * S * A.v) * den + lo_value(lo.v0), lv);
             if (store) {
                 st(d.eta1, oo, en);
                 st(d.hu1, oo, un);
@@ -661,7 +801,7 @@ __device__ __forceinline__ void finish_row(const Row &A, const F3 &Gs, const F3 
                 st_lo(d.eta1_lo, oo, le);
                 st_lo(d.hu1_lo, oo, lu);
                 st_lo(d.hv1_lo, oo, lv);
-                if (c.edge) write_frame_copies<1>(d, c, en, un, vn);
+                if (unlikely(kind & kTileEdge)) write_frame_copies<1>(cold(dk), c, en, un, vn);
             }
         } else {
             float en = A.e + dt * Me;
@@ -671,7 +811,7 @@ __device__ __forceinline__ void finish_row(const Row &A, const F3 &Gs, const F3 
                 st(d.eta1, oo, en);
                 st(d.hu1, oo, un);
                 st(d.hv1, oo, vn);
-                if (c.edge) write_frame_copies<1>(d, c, en, un, vn);
+                if (unlikely(kind & kTileEdge)) write_frame_copies<1>(cold(dk), c, en, un, vn);
             }
         }
     } else {
@@ -680,27 +820,25 @@ __device__ __forceinline__ void finish_row(const Row &A, const F3 &Gs, const F3 
         if (COMP) {
             // Q^{n+1} = Q^n + (Q* - Q^n + dt M(Q*))/2 (momenta with the
             // friction factor), the differences taken with both errors
-            const float de = (A.e - e0) + (lo.e1 - lo.e0);
-            const float du = (A.u - u0) + (lo.u1 - lo.u0);
-            const float dv = (A.v - v0) + (lo.v1 - lo.v0);
-            en = two_sum(e0, 0.5f * (de + dt * Me) + lo.e0, le);
-            un = two_sum(u0, (0.5f * (du + dt * Mu) - 0.5f * dt * S * u0) * den + lo.u0, lu);
-            vn = two_sum(v0, (0.5f * (dv + dt * Mv) - 0.5f * dt * S * v0) * den + lo.v0, lv);
+            const float de = (A.e - e0) + (lo_value(lo.e1) - lo_value(lo.e0));
+            const float du = (A.u - u0) + (lo_value(lo.u1) - lo_value(lo.u0));
+            const float dv = (A.v - v0) + (lo_value(lo.v1) - lo_value(lo.v0));
+            en = two_sum(e0, 0.5f * (de + dt * Me) + lo_value(lo.e0), le);
+            un = two_sum(u0, (0.5f * (du + dt * Mu) - 0.5f * dt * S * u0) * den + lo_value(lo.u0), lu);
+            vn = two_sum(v0, (0.5f * (dv + dt * Mv) - 0.5f * dt * S * v0) * den + lo_value(lo.v0), lv);
         } else {
             en = 0.5f * (e0 + (A.e + dt * Me));
             un = 0.5f * (u0 + (A.u + dt * Mu)) * den;
             vn = 0.5f * (v0 + (A.v + dt * Mv)) * den;
         }
-        if (fp.zone) {
-            // the boundary values are loaded here, where they are used, not
-            // at the start of the row: held across the row they would raise
-            // the register count of every tile's kernel
-            const FrsPre fl = frs_prefetch(d, c);
-            const float al = fl.al;
-            const double t = c.bs;
-            float ex[3];
-#pragma unroll
-            for (int q = 0; q < 3; ++q) ex[q] = (float)((1.0 - t) * (double)fl.a[q] + t * (double)fl.b[q]);
+        if (unlikely(kind & kTileFrs)) {
+          DomK &dc = cold(dk);
+          int best, dd;  // the nearest nested side (ties W, E, S, N)
+          frs_side(dc, c.i, c.o, best, dd);
+          if (c.out_lane && best >= 0 && dd < dc.frs_w) {
+            const float al = ft.alpha[dd];
+            const float *q = best < 2 ? ft.x[best][c.o - ft.row0] : ft.y[best - 2][c.lane];
+            const float ex[3] = {q[0], q[1], q[2]};
             if (COMP) {
                 en = two_sum(en, le + al * ((ex[0] - en) - le), le);
                 un = two_sum(un, lu + al * ((ex[1] - un) - lu), lu);
@@ -710,6 +848,7 @@ __device__ __forceinline__ void finish_row(const Row &A, const F3 &Gs, const F3 
                 un = (1.f - al) * un + al * ex[1];
                 vn = (1.f - al) * vn + al * ex[2];
             }
+          }
         }
         if (store) {
             const uint32_t so = local_off(oo);
@@ -721,23 +860,43 @@ __device__ __forceinline__ void finish_row(const Row &A, const F3 &Gs, const F3 
                 st_lo(d.hu_lo, so, lu);
                 st_lo(d.hv_lo, so, lv);
             }
-            if (c.edge) write_frame_copies<2>(d, c, en, un, vn);
+            if (unlikely(kind & kTileEdge)) write_frame_copies<2>(cold(dk), c, en, un, vn);
         }
 
-        // eq. cfl on the new state
-        float h = en + A.Hb;
-        float ri = rcp(desing(h, d));
-        float cw = fsqrt(d.g * fmaxf(h, 0.f));
-        float w = fmaxf((fabsf(un * ri) + cw) * d.rdx, (fabsf(vn * ri) + cw) * d.rdy);
+        // eq. cfl on the new state.  bit 0 of the flags: a non-finite state;
+        // bit 1: a water depth below -kappa (the scheme keeps h >= 0 under
+        // its CFL bound, so this means breakdown); both as lane masks
+        const float h = en + A.Hb;
+        bad.negative |= stored & __builtin_amdgcn_ballot_w64(h < -d.kappa);
+        const float ri = rcp(desing(h, d));
+        const float cw = fsqrt(d.g * fmaxf(h, 0.f));
+        // (with square cells the larger speed is taken first: the same value)
+        float w;
+        if (likely(d.rdx == d.rdy)) w = (fmaxf(fabsf(un), fabsf(vn)) * fabsf(ri) + cw) * d.rdx;
+        else w = fmaxf((fabsf(un * ri) + cw) * d.rdx, (fabsf(vn * ri) + cw) * d.rdy);
         wmax_loc = store ? fmaxf(wmax_loc, w) : wmax_loc;
-        // bit 0: a non-finite state; bit 1: a water depth below -kappa (the
-        // scheme keeps h >= 0 under its CFL bound, so this means breakdown);
-        // gathered over the wave by ballot, so the bits are scalar values
-        const uint64_t m_st = __builtin_amdgcn_ballot_w64(store);
-        bad.nonfinite |= m_st & (__builtin_amdgcn_ballot_w64(!isfinite(en)) | __builtin_amdgcn_ballot_w64(!isfinite(un)) |
-                                 __builtin_amdgcn_ballot_w64(!isfinite(vn)));
-        bad.negative |= m_st & __builtin_amdgcn_ballot_w64(h < -d.kappa);
+        bad.nonfinite |= stored & (__builtin_amdgcn_ballot_w64(!isfinite(en)) | __builtin_amdgcn_ballot_w64(!isfinite(un)) |
+                                   __builtin_amdgcn_ballot_w64(!isfinite(vn)));
     }
+}
+
+// the stored rounding errors of the own cell
+template <int STAGE, bool COMP, class D>
+__device__ __forceinline__ Lo load_lo(const D &d, const TileCtx &c)
+{
+    Lo lo{0u, 0u, 0u, 0u, 0u, 0u};
+    if (COMP) {
+        const uint32_t oo = cell_off(d, c.o, c.i);
+        lo.e0 = ld_lo(d.eta_lo, oo);
+        lo.u0 = ld_lo(d.hu_lo, oo);
+        lo.v0 = ld_lo(d.hv_lo, oo);
+        if (STAGE == 2) {
+            lo.e1 = ld_lo(d.eta1_lo, oo);
+            lo.u1 = ld_lo(d.hu1_lo, oo);
+            lo.v1 = ld_lo(d.hv1_lo, oo);
+        }
+    }
+    return lo;
 }
 
 // ---- one tile: a wavefront's 64 columns over rows y0..y1-1 ------------------
@@ -752,8 +911,8 @@ struct RawRow {
     float e, u, v, f, cn0, cn1, th;
 };
 
-template <bool PROJ>
-__device__ __forceinline__ RawRow load_row(const Dom &d, const float *__restrict__ E, const float *__restrict__ U,
+template <bool PROJ, class D>
+__device__ __forceinline__ RawRow load_row(const D &d, const float *__restrict__ E, const float *__restrict__ U,
                                            const float *__restrict__ V, int il, int r)
 {
     RawRow w;
@@ -769,22 +928,43 @@ __device__ __forceinline__ RawRow load_row(const Dom &d, const float *__restrict
     return w;
 }
 
-template <int STAGE, bool PROJ, bool W10, bool COMP>
-__device__ __forceinline__ void run_tile(const Dom &d, TileCtx c, int y0, int y1, bool frs, bool edge, float &wmax_loc,
-                                         BadLanes &bad)
+// Makes the compiler wait for a row's loads at this point (an empty asm that
+// reads them).
+__device__ __forceinline__ void arrived(const RawRow &r)
+{
+    asm volatile("" ::"v"(r.e), "v"(r.u), "v"(r.v), "v"(r.f), "v"(r.cn0), "v"(r.cn1), "v"(r.th));
+}
+
+// the first row of a tile and its south corners, issued before the tile's
+// other preparations
+struct TileStart {
+    RawRow row;
+    float cs0, cs1;
+};
+
+template <int STAGE, bool PROJ, class D>
+__device__ __forceinline__ TileStart load_start(const D &d, int il, int r)
+{
+    TileStart s;
+    s.row = load_row<PROJ>(d, STAGE == 1 ? d.eta : d.eta1, STAGE == 1 ? d.hu : d.hu1, STAGE == 1 ? d.hv : d.hv1, il, r);
+    const uint32_t cof = corner_off(d, r, il);
+    s.cs0 = ld(d.Hc, cof);
+    s.cs1 = ld(d.Hc, cof + 1);
+    return s;
+}
+
+template <int STAGE, bool PROJ, bool W10, bool COMP, class D>
+__device__ __forceinline__ void run_tile(const D &d, DomK *dk, FrsTable &ft, TileCtx c, const TileStart &start, int y0,
+                                         int y1,
+                                         float &wmax_loc, BadLanes &bad)
 {
     const float *__restrict__ E = STAGE == 1 ? d.eta : d.eta1;
     const float *__restrict__ U = STAGE == 1 ? d.hu : d.hu1;
     const float *__restrict__ V = STAGE == 1 ? d.hv : d.hv1;
     const int il = c.i;
-    float cs0, cs1;  // south corners of the row loaded next
-    {
-        const uint32_t cof = corner_off(d, y0 - 2, il);
-        cs0 = ld(d.Hc, cof);
-        cs1 = ld(d.Hc, cof + 1);
-    }
+    float cs0 = start.cs0, cs1 = start.cs1;  // south corners of the row loaded next
     const int klast = y1 + 1;
-    RawRow nxt = load_row<PROJ>(d, E, U, V, il, y0 - 2);
+    RawRow nxt = start.row;
 
     // B: the row below C, whose north face depth is C's south one
     auto load = [&](Row &C, const Row &B, int k) {
@@ -794,6 +974,7 @@ __device__ __forceinline__ void run_tile(const Dom &d, TileCtx c, int y0, int y1
         // loads never has to drain the prefetch of the next one
         nxt = load_row<PROJ>(d, E, U, V, il, min(k + 1, klast));
         C.e = cur.e; C.u = cur.u; C.v = cur.v; C.f = cur.f;
+        C.shallow = B.shallown;
         row_terms<PROJ>(C, cs0, cs1, cur.cn0, cur.cn1, B.Hn, cur.th, d);
         cs0 = cur.cn0;
         cs1 = cur.cn1;
@@ -802,16 +983,20 @@ __device__ __forceinline__ void run_tile(const Dom &d, TileCtx c, int y0, int y1
     Row R0, R1, R2;
     float uS, vS;
     R2.Hn = 0.5f * (cs0 + cs1);  // the face below the first row
+    R2.shallown = __builtin_amdgcn_ballot_w64(!(cs0 > d.deep));
     load(R0, R2, y0 - 2);
     load(R1, R0, y0 - 1);
     y_diff(R1, R0, d);
     load(R2, R1, y0);
     y_diff(R2, R1, d);
-    y_faces(R1, R2, R0.land, R0.anyland, d, uS, vS);
+    y_faces(R1, R2, R0.land, c.out, d, uS, vS);
+    if (R1.shallowy != 0) positivity_fix(R1.e, R1.Hn, R1.Hs, R1.eN, R1.eS);
     load(R0, R2, y0 + 1);
     y_diff(R0, R2, d);
-    y_faces(R2, R0, R1.land, R1.anyland, d, uS, vS);
-    F3 Gs = y_flux(R1, R2, uS, vS, d);
+    y_faces(R2, R0, R1.land, c.out, d, uS, vS);
+    if (R2.shallowy != 0) positivity_fix(R2.e, R2.Hn, R2.Hs, R2.eN, R2.eS);
+    F3 Gs = (R1.shallowy | R2.shallowy) == 0 ? y_flux<true, true>(R1, R2, uS, vS, d)
+                                             : y_flux<false, true>(R1, R2, uS, vS, d);
 
     // steady state: A = row k-2 (output), B = row k-1, C = row k
     auto step = [&](Row &A, Row &B, Row &C, int k) {
@@ -823,21 +1008,33 @@ __device__ __forceinline__ void run_tile(const Dom &d, TileCtx c, int y0, int y1
             u0 = ld(d.hu, oq);
             v0 = ld(d.hv, oq);
         }
-        FrsPre fp;
-        fp.zone = false;
-        if (STAGE == 2 && frs) {
-            int best, dd;
-            frs_side(d, c.i, c.o, best, dd);
-            fp.zone = c.out_lane && best >= 0 && dd < d.frs_w;
-        }
+        const Lo lo = load_lo<STAGE, COMP>(d, c);
         load(C, B, k);
         y_diff(C, B, d);
         float us, vs;
-        y_faces(B, C, A.land, A.anyland, d, us, vs);
-        F3 Gn = y_flux(A, B, us, vs, d);
+        y_faces(B, C, A.land, c.out, d, us, vs);
+        XFaces x = x_faces(A, c, d);
+        F3 Gn;
+        RowFlux rf;
+        if (likely((A.shallowy | B.shallowy | x.shallow) == 0)) {
+            if (likely((A.land | B.land) == 0)) row_fluxes<true, false>(A, B, x, us, vs, d, Gn, rf);
+            else row_fluxes<true, true>(A, B, x, us, vs, d, Gn, rf);
+        } else {
+            row_fluxes<false, true>(A, B, x, us, vs, d, Gn, rf);
+        }
+        // The next row's loads are waited for here, before the stores.  Loads
+        // and stores share one in-order counter, and the stores are behind
+        // branches: a wait after them has to assume that none was issued, and
+        // so drains those that were (1 to 3 % of stage 1).
+        arrived(nxt);
+        if (STAGE == 2 && unlikely(c.kind & kTileFrs) && c.o - y0 >= kFrsRows && (c.o - y0) % kFrsRows == 0) {
+            wave_fence();
+            frs_fill_rows(cold(dk), ft, c.x0, c.o, c.lane);
+            wave_fence();
+        }
         // a row whose output cells are all land has nothing to update
-        if (__ballot(c.out_lane && !A.land) != 0)
-            finish_row<STAGE, PROJ, W10, COMP>(A, Gs, Gn, c, e0, u0, v0, fp, d, wmax_loc, bad);
+        if ((c.out & ~A.land) != 0)
+            finish_row<STAGE, PROJ, W10, COMP>(A, Gs, Gn, rf, c, e0, u0, v0, lo, dk, ft, d, wmax_loc, bad);
         Gs = Gn;
     };
     for (int k = y0 + 2;;) {
@@ -848,7 +1045,6 @@ __device__ __forceinline__ void run_tile(const Dom &d, TileCtx c, int y0, int y1
         step(R1, R2, R0, k);
         if (++k > klast) break;
     }
-    if (edge) write_frame_nested<STAGE>(d, c, y0, y1);
 }
 
 // ---------------------------------------------------------------------------
@@ -864,7 +1060,8 @@ struct StepTime {
     bool skip, last;
 };
 
-__device__ __forceinline__ StepTime step_time(const Dom &d, int parity, double dt_fixed, int lane)
+template <class D>
+__device__ __forceinline__ StepTime step_time(const D &d, int parity, double dt_fixed, int lane)
 {
     const Ctrl *ctrl = d.ctrl;
     StepTime s;
@@ -896,6 +1093,20 @@ __device__ __forceinline__ StepTime step_time(const Dom &d, int parity, double d
     return s;
 }
 
+// The same step as stage 1 published it (advance_ctrl), read by stage 2: no
+// reduction over the 64 slots, and no division.
+template <class D>
+__device__ __forceinline__ StepTime step_published(const D &d, int parity)
+{
+    const Ctrl *ctrl = d.ctrl;
+    StepTime s;
+    s.tn = ctrl->t[parity];
+    s.dtd = ctrl->dt_step;
+    s.tnext = ctrl->t[parity ^ 1];
+    s.skip = ctrl->t_end > 0.0 && s.tn >= ctrl->t_end;
+    return s;
+}
+
 // Done by one wavefront per domain in stage 1: the slots of the next parity
 // are cleared for stage 2 to accumulate into (or, for a step past t_end, get
 // the current maximum), and the next time is published.
@@ -911,6 +1122,7 @@ __device__ __forceinline__ void advance_ctrl(Ctrl *ctrl, const StepTime &s, int 
             ctrl->t[parity ^ 1] = s.tn;
         } else {
             ctrl->t[parity ^ 1] = s.tnext;
+            ctrl->dt_step = s.dtd;
             ctrl->dt_last = (float)s.dtd;
             ctrl->steps += 1;
         }
@@ -923,16 +1135,29 @@ __device__ __forceinline__ void advance_ctrl(Ctrl *ctrl, const StepTime &s, int 
 //            then flow relaxation (eq. frs) and the CFL reduction for the
 //            next step (eq. cfl)
 // eq. rk2_semiimp; M is eq. sw_semidiscrete with the sources of eq. swe.
-template <int STAGE, bool PROJ, bool W10, bool COMP>
-__device__ __forceinline__ void process_tile(const Dom &d, const Tiling &T, int tile, int parity, const StepTime &st,
-                                             int lane)
+template <int STAGE, bool PROJ, bool W10, bool COMP, class D, class T_>
+__device__ __forceinline__ void process_tile(const D &d, DomK *dk, FrsTable &ft, const T_ &T, int tile, int parity, double dt_fixed,
+                                             bool advance, int lane)
 {
-    const double tau = STAGE == 1 ? st.tn : st.tn + st.dtd;
+    const int nx = d.nx, ny = d.ny;
+    int strip, y0, y1;
+    tile_place(T, tile, ny, strip, y0, y1);
+    const int x0 = strip * kStrip;
     TileCtx c;
+    c.i = x0 - kHalo + lane;
+    c.lane = lane;
+    c.x0 = x0;
+    c.o = y0;
+    c.out_lane = lane >= kHalo && lane < kWave - kHalo && c.i < nx;
+    c.out = __builtin_amdgcn_ballot_w64(c.out_lane);
+    c.xneed = c.out | left_in(c.out) | right_in(c.out);
+    const TileStart start = load_start<STAGE, PROJ>(d, c.i, y0 - kHalo);
+
+    const StepTime st = STAGE == 1 ? step_time(d, parity, dt_fixed, lane) : step_published(d, parity);
+    if (STAGE == 1 && advance) advance_ctrl(d.ctrl, st, parity, lane);
+    if (st.skip) return;
+    const double tau = STAGE == 1 ? st.tn : st.tn + st.dtd;
     c.dt = (float)st.dtd;
-    c.bk = 0;
-    c.bs = 0.0;
-    if (d.nb > 0) time_weights(d.nb, d.bnd_t, tau, c.bk, c.bs);
     wind_at(d, tau, c.wx, c.wy);
     c.wk = 0;
     c.ws = 0.f;
@@ -941,14 +1166,6 @@ __device__ __forceinline__ void process_tile(const Dom &d, const Tiling &T, int 
         time_weights(d.w10n, d.w10_t, tau, c.wk, s);
         c.ws = (float)s;
     }
-
-    const int nx = d.nx, ny = d.ny;
-    int strip, y0, y1;
-    tile_place(T, tile, ny, strip, y0, y1);
-    const int x0 = strip * kStrip;
-    c.i = x0 - kHalo + lane;
-    c.o = y0;
-    c.out_lane = lane >= kHalo && lane < kWave - kHalo && c.i < nx;
 
     // edge: some output cell lies within two cells of a side (its values go
     // into the frame too).  frs: some output cell lies within the relaxation
@@ -962,19 +1179,20 @@ __device__ __forceinline__ void process_tile(const Dom &d, const Tiling &T, int 
         frs |= d.bc[2] == BC_NESTED && y0 < W;
         frs |= d.bc[3] == BC_NESTED && y1 > ny - W;
     }
-    // nested frame cells are written for the time of the stage that reads
-    // them: stage 2 of this step, or stage 1 of the next
-    c.fbk = 0;
-    c.fbs = 0.0;
-    c.edge = edge;
+    c.kind = __builtin_amdgcn_readfirstlane((edge ? kTileEdge : 0) | (frs ? kTileFrs : 0) |
+                                            d.friction << kTileFriction);
     frame_copy_cols(d, c.i, c.fca, c.fcb);
-    if (edge && d.nb > 0) time_weights(d.nb, d.bnd_t, STAGE == 1 ? st.tn + st.dtd : st.tnext, c.fbk, c.fbs);
     float wmax_loc = 0.f;
     BadLanes bad{0, 0};
     // one row loop for every tile (a second variant of it in the same kernel
     // raised the register count of both by ~25 VGPRs): the relaxation zone
     // and the frame writes are uniform branches
-    run_tile<STAGE, PROJ, W10, COMP>(d, c, y0, y1, frs, edge, wmax_loc, bad);
+    // nested frame cells are written for the time of the stage that reads
+    // them: stage 2 of this step, or stage 1 of the next
+    if (edge && d.nb > 0)
+        write_frame_nested<STAGE>(cold(dk), STAGE == 1 ? st.tn + st.dtd : st.tnext, x0, y0, y1, lane);
+    if (STAGE == 2 && frs) frs_fill(cold(dk), ft, tau, x0, y0, y1, c.i, lane);
+    run_tile<STAGE, PROJ, W10, COMP>(d, dk, ft, c, start, y0, y1, wmax_loc, bad);
 
     if (STAGE == 2) {
         wmax_loc = wave_max(wmax_loc);
@@ -1002,10 +1220,11 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) void stage_kernel(Dom d, Ti
     const int b = blockIdx.x;
     const int tile = block_tile(T, b, wid);
 
-    const StepTime st = step_time(d, parity, dt_fixed, lane);
-    if (STAGE == 1 && b == 0 && wid == 0) advance_ctrl(d.ctrl, st, parity, lane);
-    if (st.skip || tile < 0) return;
-    process_tile<STAGE, PROJ, W10, COMP>(d, T, tile, parity, st, lane);
+    if (tile < 0) return;
+    // the domain block is the first kernel argument
+    DomK *dk = (DomK *)__builtin_amdgcn_kernarg_segment_ptr();
+    __shared__ FrsTable ft[kWavesPerBlock];
+    process_tile<STAGE, PROJ, W10, COMP>(d, dk, ft[wid], T, tile, parity, dt_fixed, b == 0 && wid == 0, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -1027,7 +1246,9 @@ void ensemble_kernel(const EnsMember *__restrict__ mem,
                                                                          EnsCtrl *ec, int parity, int chunk)
 {
     const int lane = threadIdx.x & (kWave - 1);
+    const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int part = blockIdx.x & (kEnsParts - 1);
+    __shared__ FrsTable ft[kWavesPerBlock];
     // reset the queue heads the next kernel of the step sequence will use:
     // stage 1 of parity p clears stage 2 of parity p, stage 2 clears stage 1
     // of parity p^1 (neither is in use while this kernel runs)
@@ -1044,12 +1265,15 @@ void ensemble_kernel(const EnsMember *__restrict__ mem,
         if (base >= len) break;
         const uint32_t end = min(base + (uint32_t)chunk, len);
         for (uint32_t j = base; j < end; ++j) {
-            const EnsItem it = items[begin + j];
-            const EnsMember &M = mem[it.member];
+            EnsItem it = items[begin + j];
+            it.member = __builtin_amdgcn_readfirstlane(it.member);
+            it.tile = __builtin_amdgcn_readfirstlane(it.tile);
+            // through the constant address space: the table does not change
+            // while the kernel runs, so its fields are scalar loads
+            const __attribute__((address_space(4))) EnsMember &M =
+                ((const __attribute__((address_space(4))) EnsMember *)(uintptr_t)mem)[it.member];
             const int p = parity ^ M.pflip;
-            const StepTime st = step_time(M.d, p, 0.0, lane);
-            if (STAGE == 1 && it.tile == 0) advance_ctrl(M.d.ctrl, st, p, lane);
-            if (!st.skip) process_tile<STAGE, PROJ, W10, COMP>(M.d, M.T, it.tile, p, st, lane);
+            process_tile<STAGE, PROJ, W10, COMP>(M.d, &M.d, ft[wid], M.T, it.tile, p, 0.0, it.tile == 0, lane);
         }
     }
 }

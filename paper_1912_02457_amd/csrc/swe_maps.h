@@ -159,14 +159,16 @@ __host__ __device__ inline void frame_corner(const Dom &d, int k, int &x, int &y
 // periodic ghost the wrapped copy (periodic sides come in pairs).  The same
 // along y for ghost rows.
 constexpr int kNoFrame = -1000;
-__host__ __device__ inline void frame_copy_cols(const Dom &d, int x, int &a, int &b)
+template <class D>
+__host__ __device__ inline void frame_copy_cols(const D &d, int x, int &a, int &b)
 {
     const int nx = d.nx;
     a = b = kNoFrame;
     if (x < 2) a = d.bc[0] == BC_WALL ? -1 - x : (d.bc[0] == BC_PERIODIC ? nx + x : kNoFrame);
     if (x >= nx - 2) b = d.bc[1] == BC_WALL ? 2 * nx - 1 - x : (d.bc[1] == BC_PERIODIC ? x - nx : kNoFrame);
 }
-__host__ __device__ inline void frame_copy_rows(const Dom &d, int y, int &a, int &b)
+template <class D>
+__host__ __device__ inline void frame_copy_rows(const D &d, int y, int &a, int &b)
 {
     const int ny = d.ny;
     a = b = kNoFrame;
@@ -203,7 +205,8 @@ __host__ __device__ inline void for_frame_targets(const Dom &d, int x, int y, F 
 
 // nearest nested side of cell (i, o) (ties W, E, S, N) and its distance in
 // cells; best = -1 without nested sides
-__host__ __device__ inline void frs_side(const Dom &d, int i, int o, int &best, int &dd)
+template <class D>
+__host__ __device__ inline void frs_side(const D &d, int i, int o, int &best, int &dd)
 {
     const int nx = d.nx, ny = d.ny;
     const int dist[4] = {i, nx - 1 - i, o, ny - 1 - o};
