@@ -230,7 +230,8 @@ int swe_diagnostics(swe_domain *d, double *mass, double *energy);
 int swe_status(swe_domain *d);
 
 /* Measures both stage kernels of this domain for rows per tile in {2..64}
- * and, around the fastest, for tails of 1-4-row bands (swe_set_stage_tiling),
+ * and, around the fastest, for tails of 1-4-row bands (swe_set_stage_tiling;
+ * on a small domain all rows but the first band),
  * then the winner under the other tile orders (a few launches each), times
  * the three fastest candidates again, and keeps the fastest tiling per
  * stage.  Before anything is timed, stage-1 launches run for about 25 ms of
@@ -244,10 +245,10 @@ int swe_autotune_tiling(swe_domain *d, int32_t *rows_per_wave);
 
 /* Work decomposition of the stage kernels: each wavefront updates a strip of
  * 60 columns over rows_per_wave rows (0 = the built-in choice per stage
- * kernel, which fills the wave slots its register use allows in whole
- * rounds); order picks the tile numbering
+ * kernel, one band height or two, from a model of how its waves fill the
+ * chip); order picks the tile numbering
  * (bit 0: row-block-major instead of strip-major, bit 1: no grouping of
- * neighbouring tiles per XCD; -1 = default).  Used by the autotuner; results
+ * neighbouring tiles per XCD; -1 = default, row-block-major).  Used by the autotuner; results
  * do not depend on it (bitwise).  swe_get_tiling reports the values and the
  * wavefronts per launch of stage kernel `stage` (1 or 2). */
 int swe_set_tiling(swe_domain *d, int32_t rows_per_wave, int32_t order);

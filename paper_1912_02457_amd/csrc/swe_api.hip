@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "swe_host.h"
+#include "swe_tiling.h"
 
 using namespace swe;
 
@@ -437,7 +438,7 @@ int swe_init_domain(const swe_params *p, void *dev_workspace, size_t bytes, void
     }
     for (int st = 0; st < 2; ++st) {
         d->wps[st] = stage_waves_per_simd(st + 1, p->north_projection != 0, p->compensated_state != 0);
-        d->T[st] = make_tiling(nx, ny, pick_rows_per_wave(nx, ny, d->cus, d->wps[st]));
+        d->T[st] = default_tiling(nx, ny, d->cus, d->wps[st]);
     }
 
     hipStream_t s = d->stream;
@@ -804,8 +805,8 @@ int swe_set_tiling(swe_domain *d, int32_t rows_per_wave, int32_t order)
     if (rows_per_wave < 0 || rows_per_wave > 4096) return fail(SWE_E_ARG, "rows_per_wave out of range");
     if (order < -1 || order > 3) return fail(SWE_E_ARG, "order must be -1 (default) or 0..3");
     for (int st = 0; st < 2; ++st) {
-        int by = rows_per_wave ? rows_per_wave : pick_rows_per_wave(d->p.nx, d->p.ny, d->cus, d->wps[st]);
-        d->T[st] = make_tiling(d->p.nx, d->p.ny, by);
+        d->T[st] = rows_per_wave ? make_tiling(d->p.nx, d->p.ny, rows_per_wave)
+                                 : default_tiling(d->p.nx, d->p.ny, d->cus, d->wps[st]);
         if (order >= 0) d->T[st].order = order;
     }
     drop_graphs(d);
@@ -904,8 +905,9 @@ void tail_candidates(const swe_domain *d, int stage, int by, std::vector<Tiling>
     for (int by2 = 1; by2 <= 4 && by2 < by; ++by2) {
         for (double rounds : {0.25, 0.5, 1.0, 2.0}) {
             const int bands = (int)std::lround(rounds * slots / nstrips);
-            const int tail = std::max(1, bands) * by2;
-            if (tail + by > ny) continue;
+            // on a domain smaller than that, all rows but one head band
+            const int tail = std::min(std::max(1, bands) * by2, ny - by);
+            if (tail <= 0) continue;
             const Tiling T = make_tiling_tail(nx, ny, by, by2, tail);
             if (T.nrb1 == T.nrb) continue;
             bool dup = false;
@@ -952,11 +954,10 @@ int sweep_stage(swe_domain *d, int stage, const Tiling &other, Tiling *best_T)
         if ((he = time_one(tails[k], &ms)) != hipSuccess) break;
         if (ms < best_ms * 0.99f) { best_ms = ms; best = tails[k]; }
     }
-    // the tile numbering of the winner: row-band-major keeps the rows that
-    // the resident waves touch close together (fewer pages in flight on
-    // large domains); without per-XCD grouping as a control
+    // the other tile numberings of the winner
     const Tiling won = best;
-    for (int order = 1; order <= 3 && he == hipSuccess; ++order) {
+    for (int order = 0; order <= 3 && he == hipSuccess; ++order) {
+        if (order == won.order) continue;
         Tiling T = won;
         T.order = order;
         float ms = 0.f;

@@ -212,6 +212,7 @@ int swe_ensemble_create(swe_domain *const *members, int32_t n, void *dev_workspa
         std::memset(&hm[k], 0, sizeof(EnsMember));
         hm[k].d = members[k]->dom;
         hm[k].T = make_tiling(members[k]->p.nx, members[k]->p.ny, by);
+        hm[k].T.order = 0;
         hm[k].pflip = members[k]->parity;
     }
     // work queue: members by size, largest first; item j -> partition j % 8

@@ -1,0 +1,134 @@
+// Host-side choice of a stage launch's tiling: the band heights (one, or a
+// head and a tail of shorter bands) whose launch a small model of the chip
+// finishes first.
+//
+// A launch is a queue of blocks of four waves, one per SIMD of a CU.  A band
+// of `by` rows costs its rows and about kBandStart more (the halo rows it
+// loads and reconstructs, the launch and the first loads).  The m blocks that
+// share a CU get through c(m) = m / (1 + kSharing (m - 1)) rows at a time:
+// one wave alone is a chain of dependent instructions, four keep the SIMD's
+// issue busy.  What decides between tilings is how the blocks fill the CUs:
+// 2.25 blocks per CU are as slow as three, and a tail of short bands evens out
+// what the tall ones leave.
+//
+// The two constants and kOneHeight are fitted to event times of both stages,
+// both state kinds, about 50 tilings of each of 15 domains from 128 x 128 to
+// 4096 x 4096 (100 x 4000 and 4000 x 100 among them): the tiling chosen is on
+// average 1.4 % slower than the best one measured, at worst 9 %.  A step in us
+// with the rule before it (work spread over the wave slots plus one wave's
+// chain, one band height, strip-major tiles) and with this one: 128 x 128
+// 13.3 and 9.6, 512 x 512 18.9 and 14.5, 1024 x 1024 beach 45 and 39, 2600 x
+// 900 coast 72 and 61 (float32 state 63 and 53), 2048 x 2048 130 and 86, 4096
+// x 4096 590 and 415.
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+#include <vector>
+
+#include "swe_device.h"
+
+namespace swe {
+
+constexpr int kMaxResident = 8;       // blocks per CU the model follows
+constexpr double kBandStart = 1.5;    // rows
+constexpr double kSharing = 0.4;
+constexpr double kOneHeight = 1.1;    // bands of one height end less evenly than the model's
+
+// CUs in the same state: `count` of them, each with n blocks, w[] rows left in each
+struct CuGroup {
+    int count, n;
+    double w[kMaxResident], since;
+};
+
+// Time (in rows of one wave) until the last of n1 blocks of c1 rows and then
+// n2 blocks of c2 rows is done, on ncu CUs with room for `room` blocks each.
+inline double launch_rows(long n1, double c1, long n2, double c2, int ncu, int room)
+{
+    std::vector<CuGroup> g;
+    g.push_back(CuGroup{ncu, 0, {}, 0.0});
+    // one more block for each CU of group k, split where the queue changes
+    auto give = [&](size_t k) {
+        while (n1 + n2 > 0) {
+            long &left = n1 > 0 ? n1 : n2;
+            const double c = n1 > 0 ? c1 : c2;
+            if (left >= g[k].count) {
+                left -= g[k].count;
+                g[k].w[g[k].n++] = c;
+                return;
+            }
+            CuGroup part = g[k];
+            part.count = (int)left;
+            part.w[part.n++] = c;
+            g[k].count -= part.count;
+            left = 0;
+            g.push_back(part);
+        }
+    };
+    auto pace = [](int n) { return 1.0 / (1.0 + kSharing * (n - 1)); };  // rows per unit of time of each block
+    for (int layer = 0; layer < room; ++layer)
+        for (size_t k = 0, m = g.size(); k < m; ++k)
+            if (g[k].n == layer) give(k);
+    double last = 0.0;
+    while (true) {
+        size_t k = g.size();
+        double t = INFINITY;
+        for (size_t q = 0; q < g.size(); ++q)
+            if (g[q].n > 0) {
+                const double e = g[q].since + *std::min_element(g[q].w, g[q].w + g[q].n) / pace(g[q].n);
+                if (e < t) { t = e; k = q; }
+            }
+        if (k == g.size()) return last;
+        last = t;
+        CuGroup &x = g[k];
+        const double done = (t - x.since) * pace(x.n);
+        int n = 0;
+        for (int q = 0; q < x.n; ++q)
+            if (x.w[q] - done > 1e-9) x.w[n++] = x.w[q] - done;
+        const int freed = x.n - n;
+        x.n = n;
+        x.since = t;
+        const size_t before = g.size();
+        for (int q = 0; q < freed && n1 + n2 > 0; ++q) {
+            give(k);
+            // a part split off still waits for its other blocks
+            for (size_t p = before; p < g.size(); ++p)
+                for (int r = g[p].n - n; r < freed && n1 + n2 > 0 && r <= q; ++r) give(p);
+        }
+    }
+}
+
+// The tiling of one stage kernel on a chip of `cus` CUs where its registers
+// allow `waves_per_simd` waves.
+inline Tiling default_tiling(int nx, int ny, int cus, int waves_per_simd)
+{
+    // taller bands save a few more halo rows and lose more in the caches: 4096
+    // x 4096 takes 413 us a step with the best tail to 16-row bands, 421 with
+    // 24, 427 with 32 (float32 state 289, 288, 289)
+    static const int heights[] = {1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 14, 16};
+    const int room = std::min(std::max(waves_per_simd, 1), kMaxResident);
+    const int nstrips = (nx + kStrip - 1) / kStrip;
+    Tiling best = make_tiling(nx, ny, 1);
+    double best_t = INFINITY;
+    auto consider = [&](const Tiling &T) {
+        // the model needs no more blocks than show how a launch ends
+        if (T.nblocks > 64L * cus * room) return;
+        const double t = launch_rows(T.nblk1, T.by + kBandStart, T.nblocks - T.nblk1, T.by2 + kBandStart, cus, room) *
+                         (T.nrb1 == T.nrb && T.by > 1 ? kOneHeight : 1.0);
+        if (t < best_t) { best_t = t; best = T; }
+    };
+    for (int by : heights) {
+        if (by > ny) break;
+        consider(make_tiling(nx, ny, by));
+        // tails of a quarter to two rounds of the wave slots
+        for (int by2 = 1; by2 <= 4 && by2 < by; ++by2)
+            for (double rounds : {0.25, 0.5, 1.0, 2.0}) {
+                const int bands = std::max(1, (int)std::lround(rounds * cus * kWavesPerBlock * room / nstrips));
+                if ((long)bands * by2 + by <= ny) consider(make_tiling_tail(nx, ny, by, by2, bands * by2));
+            }
+    }
+    if (!(best_t < INFINITY)) best = make_tiling(nx, ny, heights[sizeof(heights) / sizeof(heights[0]) - 1]);
+    return best;
+}
+
+}  // namespace swe
