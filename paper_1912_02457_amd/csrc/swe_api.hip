@@ -132,15 +132,28 @@ int swe::set_error(int code, const std::string &msg) { return fail(code, msg); }
 
 namespace {
 
-// Host-to-device uploads go through one process-wide pinned staging buffer
-// (at most 64 MiB, larger arrays go in row chunks): a copy from pageable
-// memory straight into a pitched device plane would be split by the runtime
-// into row-sized transfers.  The buffer is held for the whole upload
-// sequence of one call.
+// Copies between pageable host memory and pitched device planes go through one
+// process-wide pinned staging buffer (at most 64 MiB, or one row if that is
+// more; larger arrays go in row chunks): a direct copy would be split by the
+// runtime into row-sized transfers, and a pinned buffer per domain costs 4 ms
+// of page pinning on a domain's first read (1375 x 664 cells; the read itself
+// takes 0.6 ms).  The buffer is held for the whole copy sequence of one call.
 constexpr size_t kStageCap = (size_t)64 << 20;
 std::mutex g_stage_mu;
 char *g_stage = nullptr;
 size_t g_stage_bytes = 0;
+
+// at least `need` bytes; the caller holds g_stage_mu and has no copy in flight
+hipError_t stage_reserve(size_t need)
+{
+    if (g_stage_bytes >= need) return hipSuccess;
+    if (g_stage) (void)hipHostFree(g_stage);
+    g_stage = nullptr;
+    g_stage_bytes = 0;
+    hipError_t e = hipHostMalloc((void **)&g_stage, need, hipHostMallocDefault);
+    if (e == hipSuccess) g_stage_bytes = need;
+    return e;
+}
 
 class Uploader {
 public:
@@ -189,18 +202,65 @@ private:
             hipError_t e = flush();
             if (e != hipSuccess) return e;
         }
-        if (g_stage) (void)hipHostFree(g_stage);
-        g_stage = nullptr;
-        g_stage_bytes = 0;
-        hipError_t e = hipHostMalloc((void **)&g_stage, need, hipHostMallocDefault);
-        if (e == hipSuccess) g_stage_bytes = need;
-        return e;
+        return stage_reserve(need);
     }
     std::unique_lock<std::mutex> lk_;
     hipStream_t s_;
     size_t hint_ = 0, used_ = 0;
     bool pending_ = false;
 };
+
+// n planes of w x h floats, device rows of spitch floats, into dense pageable
+// host arrays.  What fits the staging buffer at once is copied there and moved
+// on after one wait; more goes in two halves, one filled by the device while
+// the host empties the other.
+hipError_t read_planes(hipStream_t s, int n, float *const *dst, const float *const *src, int spitch, int w, int h)
+{
+    // the steps still running on this stream are waited for before the buffer
+    // is taken: other threads' copies do not wait for them too
+    hipError_t e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> lk(g_stage_mu);
+    const size_t rowb = (size_t)w * sizeof(float), planeb = rowb * (size_t)h;
+    e = stage_reserve(std::max(rowb, std::min((size_t)n * planeb, kStageCap)));
+    if (e != hipSuccess) return e;
+    auto fetch = [&](char *to, int k, int r0, int rows) {
+        return hipMemcpy2DAsync(to, rowb, src[k] + (size_t)r0 * spitch, (size_t)spitch * sizeof(float), rowb, (size_t)rows,
+                                hipMemcpyDeviceToHost, s);
+    };
+    if ((size_t)n * planeb <= g_stage_bytes) {
+        for (int k = 0; k < n && e == hipSuccess; ++k) e = fetch(g_stage + k * planeb, k, 0, h);
+        const hipError_t w_ = hipStreamSynchronize(s);
+        if (e == hipSuccess) e = w_;
+        if (e != hipSuccess) return e;
+        for (int k = 0; k < n; ++k) std::memcpy(dst[k], g_stage + k * planeb, planeb);
+        return hipSuccess;
+    }
+    const int slots = g_stage_bytes / 2 >= rowb ? 2 : 1;
+    const size_t slotb = g_stage_bytes / slots;
+    const int rows = (int)std::min<size_t>((size_t)h, slotb / rowb);
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    for (int q = 0; q < slots && e == hipSuccess; ++q) e = hipEventCreateWithFlags(&ev[q], hipEventDisableTiming);
+    const int per = (h + rows - 1) / rows, chunks = n * per;
+    auto empty = [&](int c) {  // chunk c: wait for it, move it on
+        hipError_t x = hipEventSynchronize(ev[c % slots]);
+        const int k = c / per, r0 = (c % per) * rows;
+        if (x == hipSuccess)
+            std::memcpy(dst[k] + (size_t)r0 * w, g_stage + (size_t)(c % slots) * slotb, (size_t)std::min(rows, h - r0) * rowb);
+        return x;
+    };
+    for (int c = 0; c < chunks && e == hipSuccess; ++c) {
+        if (c >= slots) e = empty(c - slots);
+        const int k = c / per, r0 = (c % per) * rows;
+        if (e == hipSuccess) e = fetch(g_stage + (size_t)(c % slots) * slotb, k, r0, std::min(rows, h - r0));
+        if (e == hipSuccess) e = hipEventRecord(ev[c % slots], s);
+    }
+    for (int c = std::max(0, chunks - slots); c < chunks && e == hipSuccess; ++c) e = empty(c);
+    if (e != hipSuccess) (void)hipStreamSynchronize(s);  // nothing may still write the buffer
+    for (int q = 0; q < slots; ++q)
+        if (ev[q]) (void)hipEventDestroy(ev[q]);
+    return e;
+}
 
 // f of the two ghost layers of nested sides: the mirrored interior cell
 // (layer 0 <- the outermost interior cell, layer 1 <- the next one), with the
@@ -308,17 +368,26 @@ void drop_graphs(swe_domain *d)
     d->graph_objs.clear();
 }
 
-int read_ctrl(swe_domain *d, Ctrl *c)
+// the copy of the control block to pinned_ctrl, enqueued
+int start_ctrl(swe_domain *d)
 {
     if (!d->pinned_ctrl) HIP_TRY(hipHostMalloc((void **)&d->pinned_ctrl, sizeof(Ctrl), hipHostMallocDefault));
     HIP_TRY(hipMemcpyAsync(d->pinned_ctrl, d->dom.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, d->stream));
+    return SWE_OK;
+}
+
+int read_ctrl(swe_domain *d, Ctrl *c)
+{
+    int rc = start_ctrl(d);
+    if (rc) return rc;
     HIP_TRY(hipStreamSynchronize(d->stream));
     std::memcpy(c, d->pinned_ctrl, sizeof(Ctrl));
     return SWE_OK;
 }
 
-// Pinned host planes for state copies: three (eta, hu, hv), and three more
-// for their rounding errors when the state is compensated.
+// Pinned host planes for the copy of the state that the tiling sweep puts
+// back: three (eta, hu, hv), and three more for their rounding errors when the
+// state is compensated.
 int ensure_pinned_state(swe_domain *d)
 {
     if (d->pinned_state) return SWE_OK;
@@ -715,25 +784,24 @@ int swe_read_state(swe_domain *d, float *eta, float *hu, float *hv, double *t, d
     float *dst[3] = {eta, hu, hv};
     const size_t org = 2 * (size_t)d->dom.pitch + 2;  // cell (0, 0) of a framed plane
     float *src[3] = {d->dom.eta + org, d->dom.hu + org, d->dom.hv + org};
-    const size_t plane = (size_t)nx * ny;
-    bool staged[3] = {false, false, false};
+    float *to[3];
+    const float *from[3];
+    int staged = 0;
     for (int k = 0; k < 3; ++k) {
         if (!dst[k]) continue;
-        float *to = dst[k];
         if (is_pageable(dst[k])) {
-            int rc0 = ensure_pinned_state(d);
-            if (rc0) return rc0;
-            to = d->pinned_state + k * plane;
-            staged[k] = true;
+            to[staged] = dst[k];
+            from[staged++] = src[k];
+            continue;
         }
-        HIP_TRY(hipMemcpy2DAsync(to, (size_t)nx * sizeof(float), src[k], (size_t)d->dom.pitch * sizeof(float),
+        HIP_TRY(hipMemcpy2DAsync(dst[k], (size_t)nx * sizeof(float), src[k], (size_t)d->dom.pitch * sizeof(float),
                                  (size_t)nx * sizeof(float), (size_t)ny, hipMemcpyDefault, d->stream));
     }
-    Ctrl c;
-    int rc = read_ctrl(d, &c);  // also waits for the copies above
+    int rc = start_ctrl(d);
     if (rc) return rc;
-    for (int k = 0; k < 3; ++k)
-        if (staged[k]) std::memcpy(dst[k], d->pinned_state + k * plane, plane * sizeof(float));
+    if (staged > 0) HIP_TRY(read_planes(d->stream, staged, to, from, d->dom.pitch, nx, ny));
+    else HIP_TRY(hipStreamSynchronize(d->stream));
+    const Ctrl &c = *d->pinned_ctrl;
     if (t) *t = c.t[d->parity];
     if (dt_next) *dt_next = ctrl_next_dt(c, d->parity, d->dom.courant_q, d->dom.dt_interval);
     if (c.flags) return fail(SWE_E_UNSTABLE, flag_message(c.flags));
