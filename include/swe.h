@@ -293,9 +293,9 @@ const char *swe_last_error(void);
 
 /* ---- batched ensemble ---------------------------------------------------
  * Many domains of uneven sizes advanced together: each RK stage of all
- * members is ONE persistent kernel launch that drains a device queue of
- * (member, tile) work items (largest members first, split into 8
- * partitions taken in chunks with one atomic each).  Every member keeps its
+ * members is ONE kernel launch over a list of (member, tile) work items (the
+ * tall row bands of all members first, short ones last), `chunk` consecutive
+ * items to a wavefront.  Every member keeps its
  * own parameters, forcing, time and CFL time step (eq. cfl per member), so
  * a member's result is bitwise the one it gets stepped alone.  Steps are
  * replayed as captured HIP graphs.  Used for ensembles of perturbed runs and
@@ -312,7 +312,9 @@ int swe_ensemble_workspace_bytes(swe_domain *const *members, int32_t n, int32_t 
 /* Group n >= 1 ready domains (boundary data set where nested; all with the
  * same north_projection) into an ensemble using the caller's device workspace
  * (256-byte aligned, borrowed until swe_ensemble_destroy) and stream.
- * chunk = work items taken per atomic (0 = default 1).  Synchronises. */
+ * chunk = work items per wavefront (0 = default 1).  A workspace below the
+ * query's size is accepted as long as it holds the items of one band height
+ * (16 rows by default).  Synchronises. */
 int swe_ensemble_create(swe_domain *const *members, int32_t n, void *dev_workspace, size_t bytes,
                         void *hip_stream, int32_t rows_per_wave, int32_t chunk, swe_ensemble **out);
 
@@ -321,7 +323,7 @@ int swe_ensemble_create(swe_domain *const *members, int32_t n, void *dev_workspa
 int swe_ensemble_step(swe_ensemble *e, int32_t n_steps);
 
 /* Reports the work decomposition (rows per tile, chunk, work items per
- * stage, blocks of the persistent launch). */
+ * stage, blocks of a launch). */
 int swe_ensemble_info(swe_ensemble *e, int32_t *rows_per_wave, int32_t *chunk, int64_t *items, int32_t *blocks);
 
 /* HIP-event timing of the two ensemble stage kernels, as swe_stage_times. */

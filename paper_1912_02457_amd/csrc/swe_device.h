@@ -252,8 +252,6 @@ __host__ __device__ inline void tile_place(const T_ &T, int tile, int ny, int &s
 }
 
 // ---- ensemble: many domains in one launch per stage ------------------------
-constexpr int kEnsParts = 8;  // queue partitions (blocks b with b % 8 == k drain part k)
-
 struct EnsMember {
     Dom d;
     Tiling T;
@@ -267,9 +265,9 @@ struct EnsItem {
 };
 
 struct EnsCtrl {
-    uint32_t head[2][2][kEnsParts][32];  // [stage][parity][part], one 128-byte line each
-    uint32_t part_begin[kEnsParts];
-    uint32_t part_len[kEnsParts];
+    int64_t nitems;
+    int32_t nblk1;  // blocks that hold the items of the head bands
+    int32_t pad;
 };
 
 }  // namespace swe

@@ -1,11 +1,11 @@
-// Host side of the batched ensemble (include/swe.h): member table, device
-// work queue, persistent stage launches, HIP-graph replay, timing.
+// Host side of the batched ensemble (include/swe.h): member table, list of
+// work items, stage launches, HIP-graph replay, timing.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <numeric>
 
 #include "swe_host.h"
+#include "swe_tiling.h"
 
 using namespace swe;
 
@@ -21,21 +21,37 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
     } while (0)
 
 constexpr int kEnsGraphChunk = 16;
-constexpr int kDefaultRows = 16;
-// One item per atomic: the items of a member differ little in cost, and
-// taking several at once leaves the last waves of a launch with uneven
-// loads (measured on 128 served-size domains: 2.8e10 cell-updates/s with 1,
-// 2.0e10 with 4).
+// One item per wavefront: the band heights already set how long a wave runs,
+// and several items to a wave leave the last waves with uneven loads.
 constexpr int kDefaultChunk = 1;
 
 struct EnsLayout {
     size_t mem, items, ctrl, total;
 };
 
-int64_t count_items(swe_domain *const *m, int n, int by)
+using Shapes = std::vector<std::pair<int, int>>;
+
+Shapes shapes_of(swe_domain *const *m, int n)
+{
+    Shapes s;
+    for (int k = 0; k < n; ++k) s.emplace_back(m[k]->p.nx, m[k]->p.ny);
+    return s;
+}
+
+// of the current device; the workspace query and the creation must agree
+int device_cus()
+{
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+        cus = 256;
+    return cus;
+}
+
+int64_t count_items(const Shapes &shapes, const EnsBands &b)
 {
     int64_t t = 0;
-    for (int k = 0; k < n; ++k) t += make_tiling(m[k]->p.nx, m[k]->p.ny, by).ntiles;
+    for (const auto &sh : shapes) t += b.of(sh.first, sh.second).ntiles;
     return t;
 }
 
@@ -55,9 +71,14 @@ EnsLayout ens_layout(int n, int64_t items)
 
 size_t swe::ensemble_bytes_for_shapes(const std::vector<std::pair<int, int>> &shapes, int rows_per_wave)
 {
-    int by = rows_per_wave ? rows_per_wave : kDefaultRows;
-    int64_t t = 0;
-    for (auto &sh : shapes) t += make_tiling(sh.first, sh.second, by).ntiles;
+    return ens_layout((int)shapes.size(), count_items(shapes, EnsBands{rows_per_wave ? rows_per_wave : kEnsembleRows, 0, 0}))
+        .total;
+}
+
+size_t swe::ensemble_bytes_preferred(const std::vector<std::pair<int, int>> &shapes)
+{
+    int64_t t = 0;  // an item holds at least one row
+    for (const auto &sh : shapes) t += (int64_t)make_tiling(sh.first, sh.second, 1).ntiles;
     return ens_layout((int)shapes.size(), t).total;
 }
 
@@ -71,7 +92,7 @@ struct swe_ensemble {
     EnsItem *d_items = nullptr;
     EnsCtrl *d_ctrl = nullptr;
     int64_t nitems = 0;
-    int by = kDefaultRows;
+    int by = 0;
     int chunk = kDefaultChunk;
     int nblocks = 0;
     int parity = 0;
@@ -168,8 +189,8 @@ int swe_ensemble_workspace_bytes(swe_domain *const *members, int32_t n, int32_t 
     if (!members || n < 1) return set_error(SWE_E_ARG, "an ensemble needs at least one member");
     for (int k = 0; k < n; ++k)
         if (!members[k]) return set_error(SWE_E_ARG, "NULL member");
-    int by = rows_per_wave ? rows_per_wave : kDefaultRows;
-    *bytes = ens_layout(n, count_items(members, n, by)).total;
+    const Shapes shapes = shapes_of(members, n);
+    *bytes = ens_layout(n, count_items(shapes, ensemble_bands(shapes, rows_per_wave, device_cus()))).total;
     return SWE_OK;
 }
 
@@ -181,8 +202,14 @@ int swe_ensemble_create(swe_domain *const *members, int32_t n, void *dev_workspa
     if (!out || !dev_workspace || rows_per_wave < 0 || rows_per_wave > 4096 || chunk < 0 || chunk > 1024)
         return set_error(SWE_E_ARG, "bad arguments");
     if (((uintptr_t)dev_workspace) % kAlign) return set_error(SWE_E_ARG, "workspace must be 256-byte aligned");
-    int by = rows_per_wave ? rows_per_wave : kDefaultRows;
-    int64_t nitems = count_items(members, n, by);
+    const Shapes shapes = shapes_of(members, n);
+    EnsBands bands = ensemble_bands(shapes, rows_per_wave, device_cus());
+    int64_t nitems = count_items(shapes, bands);
+    if (nitems > (int64_t)1 << 31 || bytes < ens_layout(n, nitems).total) {
+        // a workspace for one band height: fewer items
+        bands = EnsBands{rows_per_wave ? rows_per_wave : kEnsembleRows, 0, 0};
+        nitems = count_items(shapes, bands);
+    }
     if (nitems > (int64_t)1 << 31) return set_error(SWE_E_ARG, "too many work items");
     EnsLayout L = ens_layout(n, nitems);
     if (bytes < L.total) return set_error(SWE_E_NOMEM, "ensemble workspace too small");
@@ -197,43 +224,34 @@ int swe_ensemble_create(swe_domain *const *members, int32_t n, void *dev_workspa
     e->d_items = (EnsItem *)(e->ws + L.items);
     e->d_ctrl = (EnsCtrl *)(e->ws + L.ctrl);
     e->nitems = nitems;
-    e->by = by;
+    e->by = bands.by;
     e->chunk = chunk ? chunk : kDefaultChunk;
     e->proj = members[0]->p.north_projection != 0;
     e->comp = members[0]->p.compensated_state != 0;
     for (int k = 0; k < n; ++k) e->w10 |= members[k]->dom.w10n > 0;
-    int w1 = ensemble_waves_per_simd(1, e->proj, e->comp), w2 = ensemble_waves_per_simd(2, e->proj, e->comp);
-    e->nblocks = members[0]->cus * std::min(w1, w2);  // one wave per SIMD per block
-    e->nblocks = (e->nblocks + kEnsParts - 1) / kEnsParts * kEnsParts;
-
     // member table
     std::vector<EnsMember> hm(n);
     for (int k = 0; k < n; ++k) {
         std::memset(&hm[k], 0, sizeof(EnsMember));
         hm[k].d = members[k]->dom;
-        hm[k].T = make_tiling(members[k]->p.nx, members[k]->p.ny, by);
-        hm[k].T.order = 0;
+        hm[k].T = bands.of(members[k]->p.nx, members[k]->p.ny);
         hm[k].pflip = members[k]->parity;
     }
-    // work queue: members by size, largest first; item j -> partition j % 8
-    std::vector<int> order(n);
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-        return (int64_t)members[a]->p.nx * members[a]->p.ny > (int64_t)members[b]->p.nx * members[b]->p.ny;
-    });
-    std::vector<std::vector<EnsItem>> parts(kEnsParts);
-    int64_t j = 0;
-    for (int k : order)
-        for (int t = 0; t < hm[k].T.ntiles; ++t, ++j) parts[j % kEnsParts].push_back(EnsItem{k, t});
+    // the items in launch order: the head bands of every member (a member's
+    // tiles in a row, so that neighbours meet in one L2), then the tail bands
     std::vector<EnsItem> items;
     items.reserve((size_t)nitems);
-    EnsCtrl hc;
-    std::memset(&hc, 0, sizeof(hc));
-    for (int p = 0; p < kEnsParts; ++p) {
-        hc.part_begin[p] = (uint32_t)items.size();
-        hc.part_len[p] = (uint32_t)parts[p].size();
-        items.insert(items.end(), parts[p].begin(), parts[p].end());
-    }
+    for (int k = 0; k < n; ++k)
+        for (int t = 0; t < hm[k].T.ntiles1; ++t) items.push_back(EnsItem{k, t});
+    const int64_t heads = (int64_t)items.size();
+    for (int k = 0; k < n; ++k)
+        for (int t = hm[k].T.ntiles1; t < hm[k].T.ntiles; ++t) items.push_back(EnsItem{k, t});
+    // blocks of four waves, a multiple of the eight XCDs
+    const int64_t per_block = (int64_t)kWavesPerBlock * e->chunk;
+    EnsCtrl hc{};
+    hc.nitems = nitems;
+    hc.nblk1 = (int32_t)((heads + per_block - 1) / per_block);
+    e->nblocks = (int)(((nitems + per_block - 1) / per_block + 7) / 8 * 8);
     hipStream_t s = e->stream;
     // member streams: everything is ordered on the ensemble stream from now on
     for (auto *m : e->members) {

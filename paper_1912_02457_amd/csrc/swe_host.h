@@ -25,13 +25,14 @@ hipError_t launch_set_t_end(Ctrl *c, double te, hipStream_t s);
 hipError_t launch_policy_reset(Ctrl *c, int parity, hipStream_t s);
 hipError_t launch_diagnostics(const Dom &d, hipStream_t s);
 int stage_waves_per_simd(int stage, bool proj, bool comp);
-int ensemble_waves_per_simd(int stage, bool proj, bool comp);
 
 int set_error(int code, const std::string &msg);  // records the message for swe_last_error
 // A member destroyed while it still belongs to an ensemble: the ensemble
 // drops it and refuses further steps.
 void ensemble_forget(swe_ensemble *e, swe_domain *d);
-// Device workspace of an ensemble whose members have these (nx, ny) shapes.
+// Device workspace of an ensemble whose members have these (nx, ny) shapes:
+// what it needs, and what lets it choose its bands freely.
+size_t ensemble_bytes_preferred(const std::vector<std::pair<int, int>> &shapes);
 size_t ensemble_bytes_for_shapes(const std::vector<std::pair<int, int>> &shapes, int rows_per_wave);
 
 struct Layout {

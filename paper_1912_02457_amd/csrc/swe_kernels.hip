@@ -1228,53 +1228,40 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) void stage_kernel(Dom d, Ti
 }
 
 // ---------------------------------------------------------------------------
-// ensemble stage kernel: many domains of uneven sizes in one persistent
-// launch.  The work items (member, tile) sit in a device queue split into 8
-// partitions; the waves of the blocks b with b % 8 == k drain partition k in
-// chunks taken with one atomicAdd each, until the partition is exhausted.
-// Every member has its own parameters, time, dt slot and CFL accumulator.
+// ensemble stage kernel: many domains of uneven sizes in one launch.  The work
+// items (member, tile) lie in one list, the tall bands of all members before
+// the short ones that end the launch; a wave takes `chunk` consecutive items,
+// and blocks are grouped per XCD like a single domain's.  The hardware hands
+// out the blocks: a persistent grid that drew its items from device queues
+// paid an atomic and two more dependent loads before every item, dealt
+// neighbouring tiles to different XCDs and ran 16-row bands whatever the size
+// (compensated state, us a step, before and now: 3 members of 0.25 M cells
+// together 70 and 16, 12 of 3.8 M 137 and 84, 20 of 6.2 M 215 and 145, 48 of
+// 13.3 M 434 and 383; float32 state 316 and 259).  Every member has its own
+// parameters, time, dt slot and CFL accumulator.
 // ---------------------------------------------------------------------------
-// Four waves per SIMD for the plain variant (128 VGPRs); the others keep
-// the compiler's choice: capped at four, the compensated stage 1 ran 23 %
-// slower with the frame copies of its edge items (A/B on the 256-member
-// workload at fixed tiles), and the literal-projection and gridded-wind
-// variants would spill.
 template <int STAGE, bool PROJ, bool W10, bool COMP>
-__global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu((PROJ || W10 || COMP) ? 1 : 4)))
-void ensemble_kernel(const EnsMember *__restrict__ mem,
-                                                                         const EnsItem *__restrict__ items,
-                                                                         EnsCtrl *ec, int parity, int chunk)
+__global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu((PROJ || W10) ? 1 : 4)))
+void ensemble_kernel(const EnsMember *__restrict__ mem, const EnsItem *__restrict__ items, const EnsCtrl *ec, int parity,
+                     int chunk)
 {
+    // member table, items and counts do not change while the kernel runs:
+    // through the constant address space they are scalar loads
+    using MemberK = const __attribute__((address_space(4))) EnsMember;
+    using ItemK = const __attribute__((address_space(4))) EnsItem;
+    using CtrlK = const __attribute__((address_space(4))) EnsCtrl;
     const int lane = threadIdx.x & (kWave - 1);
     const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-    const int part = blockIdx.x & (kEnsParts - 1);
     __shared__ FrsTable ft[kWavesPerBlock];
-    // reset the queue heads the next kernel of the step sequence will use:
-    // stage 1 of parity p clears stage 2 of parity p, stage 2 clears stage 1
-    // of parity p^1 (neither is in use while this kernel runs)
-    if (blockIdx.x == 0 && threadIdx.x < kEnsParts) {
-        if (STAGE == 1) ec->head[1][parity][threadIdx.x][0] = 0u;
-        else ec->head[0][parity ^ 1][threadIdx.x][0] = 0u;
-    }
-    const uint32_t begin = ec->part_begin[part], len = ec->part_len[part];
-    uint32_t *head = &ec->head[STAGE - 1][parity][part][0];
-    while (true) {
-        uint32_t base = 0;
-        if (lane == 0) base = atomicAdd(head, (uint32_t)chunk);
-        base = __builtin_amdgcn_readfirstlane(base);
-        if (base >= len) break;
-        const uint32_t end = min(base + (uint32_t)chunk, len);
-        for (uint32_t j = base; j < end; ++j) {
-            EnsItem it = items[begin + j];
-            it.member = __builtin_amdgcn_readfirstlane(it.member);
-            it.tile = __builtin_amdgcn_readfirstlane(it.tile);
-            // through the constant address space: the table does not change
-            // while the kernel runs, so its fields are scalar loads
-            const __attribute__((address_space(4))) EnsMember &M =
-                ((const __attribute__((address_space(4))) EnsMember *)(uintptr_t)mem)[it.member];
-            const int p = parity ^ M.pflip;
-            process_tile<STAGE, PROJ, W10, COMP>(M.d, &M.d, ft[wid], M.T, it.tile, p, 0.0, it.tile == 0, lane);
-        }
+    const CtrlK &C = *(CtrlK *)(uintptr_t)ec;
+    const int b = blockIdx.x, n1 = C.nblk1;
+    const int at = b < n1 ? xcd_group(b, n1, 0) : n1 + xcd_group(b - n1, (int)gridDim.x - n1, 0);
+    const int64_t first = ((int64_t)at * kWavesPerBlock + wid) * chunk;
+    for (int64_t j = first; j < first + chunk && j < C.nitems; ++j) {
+        const ItemK &it = ((ItemK *)(uintptr_t)items)[j];
+        const int tile = it.tile;
+        MemberK &M = ((MemberK *)(uintptr_t)mem)[it.member];
+        process_tile<STAGE, PROJ, W10, COMP>(M.d, &M.d, ft[wid], M.T, tile, parity ^ M.pflip, 0.0, tile == 0, lane);
     }
 }
 
@@ -1564,16 +1551,6 @@ hipError_t launch_ensemble(int stage, bool proj, bool w10, bool comp, const EnsM
                     : launch_ensemble_pc<1, false>(w10, comp, mem, items, ec, parity, chunk, nblocks, s, ev0, ev1);
     return proj ? launch_ensemble_pc<2, true>(w10, comp, mem, items, ec, parity, chunk, nblocks, s, ev0, ev1)
                 : launch_ensemble_pc<2, false>(w10, comp, mem, items, ec, parity, chunk, nblocks, s, ev0, ev1);
-}
-
-int ensemble_waves_per_simd(int stage, bool proj, bool comp)
-{
-    const void *f;
-    if (stage == 1) f = proj ? (comp ? (const void *)ensemble_kernel<1, true, false, true> : (const void *)ensemble_kernel<1, true, false, false>)
-                             : (comp ? (const void *)ensemble_kernel<1, false, false, true> : (const void *)ensemble_kernel<1, false, false, false>);
-    else f = proj ? (comp ? (const void *)ensemble_kernel<2, true, false, true> : (const void *)ensemble_kernel<2, true, false, false>)
-                  : (comp ? (const void *)ensemble_kernel<2, false, false, true> : (const void *)ensemble_kernel<2, false, false, false>);
-    return waves_of(f);
 }
 
 hipError_t launch_cfl(const Dom &d, int slot, hipStream_t s)

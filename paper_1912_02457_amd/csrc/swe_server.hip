@@ -231,8 +231,14 @@ int admit(swe_server *s)
         shapes.emplace_back(q->r.params.nx, q->r.params.ny);
         const size_t need = ensemble_bytes_for_shapes(shapes, s->rows);
         size_t have = s->ens_new_bytes ? s->ens_new_bytes : s->ens_bytes;
+        // room for free choice of the bands, or else for what is needed
+        const size_t most = ensemble_bytes_preferred(shapes);
         size_t grow_off = 0, grow_bytes = 0;
-        if (need > have) {
+        if (most > have) {
+            grow_bytes = align_up(most + most / 2, kAlign);
+            if (!s->arena.alloc(grow_bytes, &grow_off)) grow_bytes = 0;
+        }
+        if (!grow_bytes && need > have) {
             grow_bytes = align_up(need + need / 2, kAlign);
             if (!s->arena.alloc(grow_bytes, &grow_off)) {
                 grow_bytes = align_up(need, kAlign);

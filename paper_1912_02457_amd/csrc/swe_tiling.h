@@ -45,6 +45,10 @@ struct CuGroup {
 // n2 blocks of c2 rows is done, on ncu CUs with room for `room` blocks each.
 inline double launch_rows(long n1, double c1, long n2, double c2, int ncu, int room)
 {
+    // all but the last eight rounds of tall blocks run in step
+    const long round = (long)ncu * room, extra = std::max(0L, n1 / round - 8);
+    n1 -= extra * round;
+    const double ahead = (double)extra * c1 * (1.0 + kSharing * (room - 1));
     std::vector<CuGroup> g;
     g.push_back(CuGroup{ncu, 0, {}, 0.0});
     // one more block for each CU of group k, split where the queue changes
@@ -78,7 +82,7 @@ inline double launch_rows(long n1, double c1, long n2, double c2, int ncu, int r
                 const double e = g[q].since + *std::min_element(g[q].w, g[q].w + g[q].n) / pace(g[q].n);
                 if (e < t) { t = e; k = q; }
             }
-        if (k == g.size()) return last;
+        if (k == g.size()) return ahead + last;
         last = t;
         CuGroup &x = g[k];
         const double done = (t - x.since) * pace(x.n);
@@ -111,8 +115,6 @@ inline Tiling default_tiling(int nx, int ny, int cus, int waves_per_simd)
     Tiling best = make_tiling(nx, ny, 1);
     double best_t = INFINITY;
     auto consider = [&](const Tiling &T) {
-        // the model needs no more blocks than show how a launch ends
-        if (T.nblocks > 64L * cus * room) return;
         const double t = launch_rows(T.nblk1, T.by + kBandStart, T.nblocks - T.nblk1, T.by2 + kBandStart, cus, room) *
                          (T.nrb1 == T.nrb && T.by > 1 ? kOneHeight : 1.0);
         if (t < best_t) { best_t = t; best = T; }
@@ -127,7 +129,61 @@ inline Tiling default_tiling(int nx, int ny, int cus, int waves_per_simd)
                 if ((long)bands * by2 + by <= ny) consider(make_tiling_tail(nx, ny, by, by2, bands * by2));
             }
     }
-    if (!(best_t < INFINITY)) best = make_tiling(nx, ny, heights[sizeof(heights) / sizeof(heights[0]) - 1]);
+    return best;
+}
+
+// The bands of an ensemble's members: `by` rows, the last `tail` bands of each
+// member of by2 rows (0: one height).  The same model over all members at
+// once; rows_per_wave > 0 fixes by.
+struct EnsBands {
+    int by, by2, tail;
+    Tiling of(int nx, int ny) const { return make_tiling_tail(nx, ny, by, by2, by2 * tail); }
+};
+
+constexpr double kEnsembleStart = 1.0;  // rows more than kBandStart: the item and its member's fields
+constexpr int kEnsembleRows = 16;       // where the workspace holds no more items than these bands give
+
+template <class Shapes>  // of (nx, ny) pairs
+EnsBands ensemble_bands(const Shapes &shapes, int rows_per_wave, int cus)
+{
+    static const int heights[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16};
+    const int room = 4, nh = sizeof(heights) / sizeof(heights[0]);
+    int64_t strips = 0, rows = 0;
+    for (const auto &s : shapes) {
+        const int64_t n = (s.first + kStrip - 1) / kStrip;
+        strips += n;
+        rows += n * s.second;
+    }
+    const int64_t slots = (int64_t)cus * kWavesPerBlock * room;
+    EnsBands best{rows_per_wave ? rows_per_wave : kEnsembleRows, 0, 0};
+    const double per_slot = (double)rows / slots;
+    double best_t = INFINITY;
+    auto consider = [&](const EnsBands &b) {
+        int64_t n1 = 0, n2 = 0;
+        for (const auto &s : shapes) {
+            const Tiling T = b.of(s.first, s.second);
+            n1 += T.ntiles1;
+            n2 += T.ntiles - T.ntiles1;
+        }
+        const double start = kBandStart + kEnsembleStart;
+        const double t = launch_rows((n1 + kWavesPerBlock - 1) / kWavesPerBlock, b.by + start,
+                                     (n2 + kWavesPerBlock - 1) / kWavesPerBlock, b.by2 + start, cus, room) *
+                         (n2 == 0 && b.by > 1 ? kOneHeight : 1.0);
+        if (t < best_t) { best_t = t; best = b; }
+    };
+    for (int k = 0; k < nh; ++k) {
+        if (rows_per_wave && k > 0) break;
+        const int h = rows_per_wave ? rows_per_wave : heights[k];
+        // the best bands hold 0.4 to 3 times a wave slot's share of the rows
+        if (!rows_per_wave && k < nh - 1 && (h > 3.0 * per_slot + 1.0 || h < 0.4 * per_slot - 1.0)) continue;
+        if (!rows_per_wave && k == nh - 1 && best_t < INFINITY && h > 3.0 * per_slot + 1.0) continue;
+        consider(EnsBands{h, 0, 0});
+        for (int by2 = 1; by2 <= 4 && by2 < h; ++by2)
+            for (double rounds : {0.25, 0.5, 1.0}) {
+                const int bands = (int)std::lround(rounds * slots / strips);
+                if (bands > 0) consider(EnsBands{h, by2, bands});
+            }
+    }
     return best;
 }
 

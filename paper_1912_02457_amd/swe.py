@@ -402,8 +402,8 @@ class Domain:
 
 
 class Ensemble:
-    """Domains advanced together: one persistent launch per RK stage drains a
-    device queue of (member, tile) items over all members.  Each member keeps
+    """Domains advanced together: one launch per RK stage over the (member,
+    tile) items of all members.  Each member keeps
     its own time step; members stay usable for read_state / diagnostics and
     return to their own streams on close()."""
 
@@ -433,7 +433,7 @@ class Ensemble:
         _check(load_library().swe_ensemble_use_graphs(self._h, 1 if on else 0))
 
     def info(self):
-        """(rows per tile, items per atomic, work items per stage, blocks per launch)"""
+        """(rows per tile, items per wavefront, work items per stage, blocks per launch)"""
         r, c, i, b = C.c_int32(), C.c_int32(), C.c_int64(), C.c_int32()
         _check(load_library().swe_ensemble_info(self._h, C.byref(r), C.byref(c), C.byref(i), C.byref(b)))
         return r.value, c.value, i.value, b.value

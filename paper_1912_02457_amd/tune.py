@@ -1,9 +1,9 @@
 """Measured choice of the ensemble's work decomposition.
 
-The persistent ensemble kernel takes two knobs: rows per tile (the strip
+The ensemble kernel takes two knobs: rows per tile (the strip
 height one wavefront sweeps; taller tiles amortise the 4-row halo of the
-two-row stencil, shorter ones balance the tail of the queue) and the number
-of work items a wavefront claims per atomic.  ``autotune_ensemble`` times a
+two-row stencil, shorter ones balance the end of the launch) and the number
+of consecutive work items a wavefront takes.  ``autotune_ensemble`` times a
 few steps of every candidate on the real members and keeps the fastest; the
 result is cached on disk under a key made of the member shapes, so a
 repeated ensemble of the same shapes skips the sweep.
