@@ -36,15 +36,33 @@ using swe::set_error;
 // row a-1 computes the misfit of cell row a-1, the slopes and corner
 // contributions of cell row a-2, the corrected corners of row a-2 and the
 // smoothed output row a-3.  Neighbouring columns come through DPP lane
-// shifts; the next row's loads are issued before the current row is used.
+// shifts.
+//
+// A round moves 13 bytes a corner through memory and is bound by that on large
+// grids and by the launch on small ones, once the instructions of a row are
+// few: water flags are 64-bit scalars of a row, shifted and counted on the
+// scalar unit, the limiter is one median, addresses are buffer accesses with a
+// scalar row offset, and a segment with no row or lane outside the domain has
+// a body without the tests for it.  33 vector instructions a row and 71 before;
+// microseconds a round before and now: 100 x 100 5.5 and 4.1, 1202 x 602 6.8
+// and 5.5, 2600 x 900 11.1 and 7.9, 4000 x 2400 31.7 and 20.6 (6.1 TB/s).
 constexpr int RSTRIP = 58;
 
 constexpr int kDppShl1 = 0x130;  // wave_shl:1 -- value of lane + 1
 constexpr int kDppShr1 = 0x138;  // wave_shr:1 -- value of lane - 1
-__device__ __forceinline__ int lane_right(int v) { return __builtin_amdgcn_update_dpp(0, v, kDppShl1, 0xF, 0xF, false); }
-__device__ __forceinline__ int lane_left(int v) { return __builtin_amdgcn_update_dpp(0, v, kDppShr1, 0xF, 0xF, false); }
-__device__ __forceinline__ float lane_right(float v) { return __int_as_float(lane_right(__float_as_int(v))); }
-__device__ __forceinline__ float lane_left(float v) { return __int_as_float(lane_left(__float_as_int(v))); }
+// 0 past the ends of the wave; in this form the shift joins the instruction
+// that uses it
+__device__ __forceinline__ float lane_right(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kDppShl1, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float lane_left(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kDppShr1, 0xF, 0xF, true));
+}
+
+using Mask = uint64_t;  // bit l = lane l
+__device__ __forceinline__ bool in(Mask m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
 // Element access through a 32-bit byte offset from a uniform base pointer
 // (the scalar-base + vector-offset addressing form; no 64-bit address
@@ -62,10 +80,14 @@ __device__ __forceinline__ void stf(float *__restrict__ base, uint32_t i, float 
     *reinterpret_cast<float *>(reinterpret_cast<char *>(base) + (i << 2)) = v;
 }
 
-__device__ __forceinline__ float minmod2(float a, float b)
+// The limited slope of two differences: the smaller one where both have one
+// sign, else 0, which is the median of the two and 0.  The median of a NaN is
+// not 0: a difference is taken through `difference`, which makes it 0.
+__device__ __forceinline__ float minmod2(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, 0.0f); }
+__device__ __forceinline__ float difference(Mask both, float a, float b)
 {
-    const float mn = fminf(a, b), mx = fmaxf(a, b);
-    return ((a > 0.0f) & (b > 0.0f)) ? mn : (((a < 0.0f) & (b < 0.0f)) ? mx : 0.0f);
+    const float d = a - b;
+    return in(both & __builtin_amdgcn_ballot_w64(d == d)) ? d : 0.0f;
 }
 
 // Blocks go to the 8 XCDs round-robin; give each XCD a contiguous run of
@@ -76,6 +98,148 @@ __device__ __forceinline__ int xcd_block(int b, int n)
     return x * q + min(x, r) + k;
 }
 
+// this wave's work item, the same in all its lanes
+__device__ __forceinline__ int wave_item()
+{
+    return xcd_block(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y) * 4 +
+           __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+}
+
+// A plane as a buffer: an access adds a scalar row offset and a lane's column
+// offset in the load itself, so an address costs no vector instruction.
+// Every plane stays below 4 GiB; accesses past its end read 0 or are dropped.
+struct Plane {
+    __amdgpu_buffer_rsrc_t r;
+    uint32_t pitch;  // bytes of a row
+    __device__ __forceinline__ Plane(const void *p, uint32_t row_bytes, uint32_t rows)
+        : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)(row_bytes * rows), 0x00020000)),
+          pitch(row_bytes)
+    {
+    }
+    __device__ __forceinline__ float f32(int row, uint32_t col) const
+    {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, col << 2, (uint32_t)row * pitch, 0));
+    }
+    __device__ __forceinline__ int byte(int row, uint32_t col) const
+    {
+        return (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(r, col, (uint32_t)row * pitch, 0);
+    }
+    __device__ __forceinline__ void put(int row, uint32_t col, float v) const
+    {
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, col << 2, (uint32_t)row * pitch, 0);
+    }
+};
+
+// INSIDE: no lane or row of the segment lies outside the domain
+template <bool INIT, bool INSIDE, int R>
+__device__ __forceinline__ void recon_rows(int nx, int ny, int J0, int I0, const float *__restrict__ Hm,
+                                           const uint8_t *__restrict__ land, const float *__restrict__ Hin, float w,
+                                           float *__restrict__ Hout)
+{
+    constexpr int NS = R + 6;  // steps: three warm-up rows below, three above
+    const int lane = threadIdx.x & 63, I = I0 + lane;
+    const uint32_t Ic = (uint32_t)(INSIDE ? I : min(max(I, 0), nx));
+    const uint32_t ic = (uint32_t)(INSIDE ? I : min(max(I, 0), nx - 1));
+    const uint32_t nxc = (uint32_t)nx + 1;
+    const Plane corners_in(Hin, nxc * 4u, (uint32_t)ny + 1), corners_out(Hout, nxc * 4u, (uint32_t)ny + 1);
+    const Plane cells(Hm, (uint32_t)nx * 4u, (uint32_t)ny), mask(land, (uint32_t)nx, (uint32_t)ny);
+    const Mask cols = INSIDE ? ~(Mask)0 : __builtin_amdgcn_ballot_w64(I >= 0 && I < nx);
+    const Mask west = __builtin_amdgcn_ballot_w64(I <= 0), east = __builtin_amdgcn_ballot_w64(I >= nx);
+    const float wq = 0.25f * w, wp = 1.0f - w;
+    const int a0 = J0 - 3;
+
+    // every load of the segment first (clamped rows: always valid
+    // addresses), so the wave waits for memory once, not once per row; a row's
+    // base is scalar, a lane adds its column
+    float Hb[NS], Mb[NS];
+    int Lb[NS];
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+        const int rc = INSIDE ? a0 + k : min(max(a0 + k, 0), ny);
+        const int rm = INSIDE ? a0 + k - 1 : min(max(a0 + k - 1, 0), ny - 1);
+        Hb[k] = INIT ? 0.f : corners_in.f32(rc, Ic);
+        Mb[k] = cells.f32(rm, ic);
+        Lb[k] = 0;
+    }
+    if (land) {
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+            const int rm = INSIDE ? a0 + k - 1 : min(max(a0 + k - 1, 0), ny - 1);
+            Lb[k] = mask.byte(rm, ic);
+        }
+    }
+    // all of them have arrived here: without this the compiler moves a row's
+    // loads to where the row is used, one wait each
+#pragma unroll
+    for (int k = 0; k < NS; ++k) asm volatile("" : "+v"(Hb[k]), "+v"(Mb[k]), "+v"(Lb[k]));
+
+    // pipeline registers; names give the row relative to the newest corner row a
+    float H1 = 0.f, H2 = 0.f, S1 = 0.f;        // corners a-1, a-2; sum of corner a-1 and its right neighbour
+    float D2 = 0.f, Y2 = 0.f;                  // misfit of cell row a-2 (0 off the water); its difference to row a-3
+    Mask W2 = 0;                               // water flags of cell row a-2
+    Mask X3 = 0, B3 = 0, O3 = 0, O4 = 0;       // rows a-3, a-4: one, both, any of a cell and its left neighbour water
+    float UR3 = 0.f, UL3 = 0.f;                // cell row a-3: estimates at its upper corners
+    float P3 = 0.f, P4 = 0.f;                  // corrected corners of rows a-3, a-4
+    float M1 = 0.f, N2 = 0.f, N3 = 0.f;        // cell values, row a-2; sum with the left neighbour, rows a-3, a-4
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+        const int a = a0 + k;
+        const float Ha = Hb[k], Mc = Mb[k];
+
+        // misfit of cell row a-1
+        const Mask W1 = (INSIDE || (a - 1 >= 0 && a - 1 < ny)) ? cols & __builtin_amdgcn_ballot_w64(Lb[k] == 0) : 0;
+        const float S0 = lane_right(Ha) + Ha;
+        const float misfit = INIT ? Mc : __builtin_fmaf(-0.25f, S1 + S0, Mc);
+        const float D1 = in(W1) ? misfit : 0.f;
+
+        // slopes and corner estimates of cell row a-2; all 0 off the water
+        const float Dr = lane_right(D2);
+        const float dx = difference(W2 & (W2 >> 1), Dr, D2), Y1 = difference(W2 & W1, D1, D2);
+        const float sx = 0.5f * minmod2(lane_left(dx), dx), sy = 0.5f * minmod2(Y2, Y1);
+        const float U = D2 + sy, L = D2 - sy;
+        const float UR2 = U + sx, UL2 = U - sx, DR2 = L + sx, DL2 = L - sx;
+
+        // corrected corner row a-2: the mean over the water cells among
+        // (a-3, I-1), (a-3, I), (a-2, I-1), (a-2, I).  Cells off the water add
+        // 0; the number of water cells is summed bit by bit in the masks
+        const Mask W2l = W2 << 1, X2 = W2 ^ W2l, B2 = W2 & W2l, O2 = W2 | W2l;
+        const Mask odd = X3 ^ X2, two = B3 ^ B2 ^ (X3 & X2), four = B3 & B2;
+        const float acc = lane_left(UR3) + UL3 + (lane_left(DR2) + DL2);
+        float share = in(four) ? 0.25f : 1.0f;
+        share = in(two) ? 0.5f : share;
+        share = in(two & odd) ? 1.0f / 3.0f : share;
+        const float P2 = INIT ? acc * share : __builtin_fmaf(acc, share, H2);
+
+        // output row Y = a-3 (the first six steps only fill the pipeline)
+        const int Y = a - 3;
+        const float N1 = lane_left(M1) + M1;
+        if (k >= 6) {
+            float out = P3;
+            if (!INIT) {
+                const float up = (INSIDE || Y < ny) ? P2 : P3, down = (INSIDE || Y > 0) ? P4 : P3;
+                float left = lane_left(P3), right = lane_right(P3);
+                if (!INSIDE) {
+                    left = in(west) ? P3 : left;
+                    right = in(east) ? P3 : right;
+                }
+                out = __builtin_fmaf(wp, P3, wq * ((up + down) + left + right));
+            }
+            float fill = 0.25f * (N3 + N2);
+            asm("" : "+v"(out), "+v"(fill));  // both computed, then chosen: no branch
+            out = in(O4 | O3) ? out : fill;
+            if (lane >= 3 && lane < 3 + RSTRIP && (INSIDE || (I <= nx && Y <= ny))) 
+                corners_out.put(Y, (uint32_t)I, out);
+        }
+
+        H2 = H1; H1 = Ha; S1 = S0;
+        D2 = D1; Y2 = Y1;
+        W2 = W1; X3 = X2; B3 = B2; O4 = O3; O3 = O2;
+        UR3 = UR2; UL3 = UL2;
+        P4 = P3; P3 = P2;
+        N3 = N2; N2 = N1; M1 = Mc;
+    }
+}
+
 template <bool INIT, int R>
 __global__ __launch_bounds__(256) void recon_round_kernel(int nx, int ny, int nsx, int nitems,
                                                           const float *__restrict__ Hm,
@@ -83,104 +247,21 @@ __global__ __launch_bounds__(256) void recon_round_kernel(int nx, int ny, int ns
                                                           const float *__restrict__ Hin, float w,
                                                           float *__restrict__ Hout)
 {
-    constexpr int NS = R + 6;  // steps: three warm-up rows below, three above
-    const int lane = threadIdx.x & 63;
-    // the wave's index is the same in all its lanes: read it as a scalar, so
-    // that the row offsets below are scalar too and every load and store is
-    // a scalar row base plus the lane's column
-    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int item = xcd_block(blockIdx.x, gridDim.x) * 4 + wv;
+    const int item = wave_item();
     if (item >= nitems) return;  // whole waves leave together
-    const int J0 = (item / nsx) * R, I = (item % nsx) * RSTRIP - 3 + lane;
-    const uint32_t Ic = (uint32_t)min(max(I, 0), nx), ic = (uint32_t)min(max(I, 0), nx - 1);
-    const bool col_in = I >= 0 && I < nx;
-    const bool store = lane >= 3 && lane < 3 + RSTRIP && I <= nx;
-    const uint32_t nxc = (uint32_t)nx + 1;
-    const float wq = 0.25f * w, wp = 1.0f - w;
-    const int a0 = J0 - 3;
-
-    // every load of the segment first (clamped rows: always valid
-    // addresses), so the wave waits for memory once, not once per row
-    float Hb[NS], Mb[NS];
-    int Lb[NS];
-#pragma unroll
-    for (int k = 0; k < NS; ++k) {
-        const uint32_t rc = (uint32_t)min(max(a0 + k, 0), ny), rm = (uint32_t)min(max(a0 + k - 1, 0), ny - 1);
-        Hb[k] = INIT ? 0.f : ldf(Hin, rc * nxc + Ic);
-        Mb[k] = ldf(Hm, rm * (uint32_t)nx + ic);
-        Lb[k] = 0;
-    }
-    if (land) {
-#pragma unroll
-        for (int k = 0; k < NS; ++k)
-            Lb[k] = ldb(land, (uint32_t)min(max(a0 + k - 1, 0), ny - 1) * (uint32_t)nx + ic);
-    }
-
-    // pipeline registers; names give the row relative to the newest corner row a
-    float H1 = 0.f, H1r = 0.f, H2 = 0.f;       // corners a-1 (and its right neighbour), a-2
-    float D2 = 0.f, D3 = 0.f;                  // misfit of cell rows a-2, a-3
-    int W2 = 0, W3 = 0, W4 = 0, W3l = 0, W4l = 0;  // water flags (l: of the cell to the left)
-    float UR3 = 0.f, UL3 = 0.f;                // cell row a-3: estimates at its upper corners
-    float P3 = 0.f, P4 = 0.f;                  // corrected corners of rows a-3, a-4
-    float M1 = 0.f, M2 = 0.f, M3 = 0.f;        // clamped cell values, rows a-2, a-3, a-4
-#pragma unroll
-    for (int k = 0; k < NS; ++k) {
-        const int a = a0 + k;
-        const float Ha = Hb[k], Mc = Mb[k];
-
-        // misfit of cell row a-1
-        const int W1 = ((a - 1 >= 0) & (a - 1 < ny) & col_in & (Lb[k] == 0)) ? 1 : 0;
-        const float Har = lane_right(Ha);
-        const float D1 = W1 ? (INIT ? Mc : Mc - 0.25f * (H1 + H1r + Ha + Har)) : 0.f;
-
-        // slopes and corner estimates of cell row a-2
-        const float Dl = lane_left(D2), Dr = lane_right(D2);
-        const int W2l = lane_left(W2), W2r = lane_right(W2);
-        const float sx = minmod2(W2l ? D2 - Dl : 0.f, W2r ? Dr - D2 : 0.f);
-        const float sy = minmod2(W3 ? D2 - D3 : 0.f, W1 ? D1 - D2 : 0.f);
-        const float UR2 = D2 + 0.5f * sx + 0.5f * sy, UL2 = D2 - 0.5f * sx + 0.5f * sy;
-        const float DR2 = D2 + 0.5f * sx - 0.5f * sy, DL2 = D2 - 0.5f * sx - 0.5f * sy;
-
-        // corrected corner row a-2: cells (a-3, I-1), (a-3, I), (a-2, I-1), (a-2, I)
-        const float UR3l = lane_left(UR3), DR2l = lane_left(DR2);
-        // absent cells add +0, which leaves the running sum unchanged;
-        // dividing by 1, 2 or 4 is exact, by 3 within one rounding
-        const float acc = (((W3l ? UR3l : 0.f) + (W3 ? UL3 : 0.f)) + (W2l ? DR2l : 0.f)) + (W2 ? DL2 : 0.f);
-        const int cnt = W3l + W3 + W2l + W2;
-        const float est = acc * (cnt == 4 ? 0.25f : cnt == 3 ? 1.0f / 3.0f : cnt == 2 ? 0.5f : 1.0f);
-        const float P2 = INIT ? est : H2 + est;
-
-        // output row Y = a-3 (the first six steps only fill the pipeline)
-        const int Y = a - 3;
-        if (k >= 6) {
-            const float P3l = lane_left(P3), P3r = lane_right(P3);
-            const float M2l = lane_left(M2), M3l = lane_left(M3);
-            const bool keep = (W4l | W4 | W3l | W3) != 0;
-            const float fill = 0.25f * (M3l + M3 + M2l + M2);
-            const float sm = (I > 0 ? P3l : P3) + (I < nx ? P3r : P3) + (Y > 0 ? P4 : P3) + (Y < ny ? P2 : P3);
-            const float out = keep ? (INIT ? P3 : wp * P3 + wq * sm) : fill;
-            if (store & (Y <= ny)) stf(Hout, (uint32_t)Y * nxc + (uint32_t)I, out);
-        }
-
-        H2 = H1; H1 = Ha; H1r = Har;
-        D3 = D2; D2 = D1;
-        W4 = W3; W3 = W2; W2 = W1; W4l = W3l; W3l = W2l;
-        UR3 = UR2; UL3 = UL2;
-        P4 = P3; P3 = P2;
-        M3 = M2; M2 = M1; M1 = Mc;
-    }
+    const int seg = item / nsx, J0 = seg * R, I0 = (item - seg * nsx) * RSTRIP - 3;
+    if (I0 >= 0 && I0 + 63 < nx && J0 >= 4 && J0 + R + 1 < ny)
+        recon_rows<INIT, true, R>(nx, ny, J0, I0, Hm, land, Hin, w, Hout);
+    else
+        recon_rows<INIT, false, R>(nx, ny, J0, I0, Hm, land, Hin, w, Hout);
 }
 
 template <bool INIT>
 hipError_t launch_recon_round(int R, unsigned blocks, hipStream_t s, int nx, int ny, int nsx, int items,
                               const float *Hm, const uint8_t *land, const float *Hin, float w, float *Hout)
 {
-    if (R == 16)
-        hipLaunchKernelGGL((recon_round_kernel<INIT, 16>), dim3(blocks), dim3(256), 0, s, nx, ny, nsx, items, Hm,
-                           land, Hin, w, Hout);
-    else
-        hipLaunchKernelGGL((recon_round_kernel<INIT, 8>), dim3(blocks), dim3(256), 0, s, nx, ny, nsx, items, Hm,
-                           land, Hin, w, Hout);
+    auto *kernel = R == 4 ? recon_round_kernel<INIT, 4> : recon_round_kernel<INIT, 8>;
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, nx, ny, nsx, items, Hm, land, Hin, w, Hout);
     return hipGetLastError();
 }
 
@@ -222,15 +303,6 @@ __device__ __forceinline__ void stb2(uint8_t *base, uint32_t i, uint32_t v)
 {
     *reinterpret_cast<u8x2 *>(base + i) = (uint16_t)v;
 }
-
-// this wave's work item, the same in all its lanes
-__device__ __forceinline__ int wave_item()
-{
-    return xcd_block(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y) * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-}
-
-using Mask = uint64_t;  // bit l = lane l
-__device__ __forceinline__ bool in(Mask m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
 // ---------------------------------------------------------------------------
 // Land erosion: a land cell with a water 4-neighbour (outside = land) turns
@@ -545,10 +617,12 @@ extern "C" int swe_reconstruct_bathymetry(int32_t nx, int32_t ny, const float *H
     if (iters > 0 && !scratch) return set_error(SWE_E_ARG, "scratch is required when iters > 0");
     if (!(smooth >= 0.0f && smooth <= 1.0f)) return set_error(SWE_E_ARG, "smooth must be in [0, 1]");
     hipStream_t s = (hipStream_t)hip_stream;
-    // rows per segment: 16 when that still gives about four waves per SIMD,
-    // else 8 (more waves, more warm-up rows)
+    // rows per segment: 8, or 4 while 8 would give a SIMD fewer than two waves
+    // (six warm-up rows a segment; microseconds a round with 4 and 8 rows:
+    // 500 x 1000 4.8 and 5.4, 1202 x 602 5.5 and 5.6, 2600 x 900 8.8 and 7.9;
+    // 12 and more are slower at every size)
     const int nsx = (nx + 1 + RSTRIP - 1) / RSTRIP;
-    const int R = (int64_t)nsx * ((ny + 1 + 15) / 16) >= 4096 ? 16 : 8;
+    const int R = (int64_t)nsx * ((ny + 1 + 7) / 8) >= 2048 ? 8 : 4;
     const int nsy = (ny + 1 + R - 1) / R;
     const int64_t items = (int64_t)nsx * nsy;
     if (items > INT32_MAX / 2) return set_error(SWE_E_ARG, "domain too large");

@@ -2,12 +2,13 @@
 segments of rows end: one column or row either side of each, fields that lie
 unaligned inside larger arrays, land bytes other than 1, NaN behind land.
 Masks, erosion and sampled corners are exact; refined and averaged values
-take 2-4 float32 roundings of values of size max|v|: 1e-6 max|v|."""
+take 2-4 float32 roundings of values of size max|v|: 1e-6 max|v|.  Corner
+depths: 16 float32 roundings a round, 2e-5 max|Hm| as over the 11 rounds there."""
 
 import numpy as np
 import pytest
 
-from test_gpu_preprocess import FIELD_TOL, P, _cuda, _host, swe  # noqa: F401
+from test_gpu_preprocess import FIELD_TOL, RECON_TOL, P, _cuda, _host, swe  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -55,6 +56,23 @@ def test_strip_edges(swe, nx, ny, put):  # noqa: F811
         assert np.abs(_host(cf) - np.stack(of)).max() <= FIELD_TOL * np.abs(X).max()
         assert m is None or np.array_equal(_host(cl), ol)
         assert np.array_equal(_host(ch).astype(np.float64), oh)
+
+
+@pytest.mark.parametrize("land_on", [True, False])
+@pytest.mark.parametrize("nx,ny", [(57, 12), (58, 3), (59, 13), (66, 9), (67, 17), (125, 10), (183, 29), (60, 9001)])
+def test_corner_depths_at_strip_edges(swe, nx, ny, land_on):  # noqa: F811
+    """One strip to four, segments with and without rows outside the domain,
+    the short and (last size) the long segments, odd and even rounds."""
+    print(nx, ny, land_on, flush=True)
+    rng = np.random.default_rng(nx + ny)
+    Hm = rng.uniform(5.0, 80.0, (ny, nx)).astype(np.float32)
+    land = (rng.uniform(size=(ny, nx)) < 0.3).astype(np.uint8) if land_on else None
+    if land_on:
+        land[:, nx // 3:nx // 3 + 6] = 200  # corners that touch no water
+    for iters in (0, 1, 2, 5) if ny < 9000 else (2,):
+        ref = P.reconstruct_bathymetry(Hm, None if land is None else (land != 0).astype(np.uint8), iters=iters)
+        got = _host(swe.reconstruct_bathymetry(_cuda(Hm), None if land is None else _cuda(land), iters=iters))
+        assert np.abs(got - ref).max() <= RECON_TOL * np.abs(Hm).max()
 
 
 def test_land_values_stay_behind_the_mask(swe):  # noqa: F811
