@@ -36,17 +36,21 @@ using swe::set_error;
 // row a-1 computes the misfit of cell row a-1, the slopes and corner
 // contributions of cell row a-2, the corrected corners of row a-2 and the
 // smoothed output row a-3.  Neighbouring columns come through DPP lane
-// shifts.
+// shifts.  Two rounds to a launch double the halo (strips of 52, lanes 6..57)
+// and the warm-up rows and halve the launches and the corners' traffic.
 //
-// A round moves 13 bytes a corner through memory and is bound by that on large
-// grids and by the launch on small ones, once the instructions of a row are
-// few: water flags are 64-bit scalars of a row, shifted and counted on the
-// scalar unit, the limiter is one median, addresses are buffer accesses with a
-// scalar row offset, and a segment with no row or lane outside the domain has
-// a body without the tests for it.  33 vector instructions a row and 71 before;
-// microseconds a round before and now: 100 x 100 5.5 and 4.1, 1202 x 602 6.8
-// and 5.5, 2600 x 900 11.1 and 7.9, 4000 x 2400 31.7 and 20.6 (6.1 TB/s).
-constexpr int RSTRIP = 58;
+// What bounds a round is the launch on small grids and memory (13 bytes a
+// corner) on large ones, once the instructions of a row are few: water flags
+// are 64-bit scalars of a row, shifted and counted on the scalar unit, the
+// limiter is one median, addresses are buffer accesses with a scalar row
+// offset, and a segment with no row or lane outside the domain has a body
+// without the tests for it.  29 vector instructions a row and round, 71
+// before; microseconds a round with the rounds one by one before that, one by
+// one after it, and in pairs: 100 x 100 5.5, 4.1 and 2.8; 1202 x 602 6.8, 5.5
+// and 4.4; 2600 x 900 11.1, 7.9 and 7.5; 4000 x 2400 31.7, 20.6 (6.1 TB/s)
+// and 17.4.
+constexpr int halo(bool pair) { return pair ? 6 : 3; }  // columns and rows on each side
+constexpr int strip(bool pair) { return 64 - 2 * halo(pair); }
 
 constexpr int kDppShl1 = 0x130;  // wave_shl:1 -- value of lane + 1
 constexpr int kDppShr1 = 0x138;  // wave_shr:1 -- value of lane - 1
@@ -130,13 +134,84 @@ struct Plane {
     }
 };
 
-// INSIDE: no lane or row of the segment lies outside the domain
-template <bool INIT, bool INSIDE, int R>
+// Lanes of a wave at or beyond the first and last corner column.
+struct SideLanes { Mask west, east; };
+
+// One round of a wave as a pipeline over its rows: `next` takes corner row a
+// and cell row a-1 (values, water flags) and gives row a-3 of the round's
+// result, from the seventh row on.  INSIDE: no lane or row lies outside the
+// domain.  Names give the row relative to the newest corner row a.
+template <bool INIT, bool INSIDE>
+struct Round {
+    float H1 = 0.f, H2 = 0.f, S1 = 0.f;   // corners a-1, a-2; sum of corner a-1 and its right neighbour
+    float D2 = 0.f, Y2 = 0.f;             // misfit of cell row a-2 (0 off the water); its difference to row a-3
+    Mask W2 = 0;                          // water flags of cell row a-2
+    Mask X3 = 0, B3 = 0, O3 = 0, O4 = 0;  // rows a-3, a-4: one, both, any of a cell and its left neighbour water
+    float UR3 = 0.f, UL3 = 0.f;           // cell row a-3: estimates at its upper corners
+    float P3 = 0.f, P4 = 0.f;             // corrected corners of rows a-3, a-4
+    float M1 = 0.f, N2 = 0.f, N3 = 0.f;   // cell values, row a-2; sum with the left neighbour, rows a-3, a-4
+
+    __device__ __forceinline__ float next(int a, int ny, const SideLanes &side, float w, float Ha, float Mc, Mask W1)
+    {
+        // misfit of cell row a-1
+        const float S0 = lane_right(Ha) + Ha;
+        const float misfit = INIT ? Mc : __builtin_fmaf(-0.25f, S1 + S0, Mc);
+        const float D1 = in(W1) ? misfit : 0.f;
+
+        // slopes and corner estimates of cell row a-2; all 0 off the water
+        const float Dr = lane_right(D2);
+        const float dx = difference(W2 & (W2 >> 1), Dr, D2), Y1 = difference(W2 & W1, D1, D2);
+        const float sx = 0.5f * minmod2(lane_left(dx), dx), sy = 0.5f * minmod2(Y2, Y1);
+        const float U = D2 + sy, L = D2 - sy;
+        const float UR2 = U + sx, UL2 = U - sx, DR2 = L + sx, DL2 = L - sx;
+
+        // corrected corner row a-2: the mean over the water cells among
+        // (a-3, I-1), (a-3, I), (a-2, I-1), (a-2, I).  Cells off the water add
+        // 0; the number of water cells is summed bit by bit in the masks
+        const Mask W2l = W2 << 1, X2 = W2 ^ W2l, B2 = W2 & W2l, O2 = W2 | W2l;
+        const Mask odd = X3 ^ X2, two = B3 ^ B2 ^ (X3 & X2), four = B3 & B2;
+        const float acc = lane_left(UR3) + UL3 + (lane_left(DR2) + DL2);
+        float share = in(four) ? 0.25f : 1.0f;
+        share = in(two) ? 0.5f : share;
+        share = in(two & odd) ? 1.0f / 3.0f : share;
+        const float P2 = INIT ? acc * share : __builtin_fmaf(acc, share, H2);
+
+        // result row Y = a-3
+        const int Y = a - 3;
+        const float N1 = lane_left(M1) + M1;
+        float out = P3;
+        if (!INIT) {
+            const float up = (INSIDE || Y < ny) ? P2 : P3, down = (INSIDE || Y > 0) ? P4 : P3;
+            float left = lane_left(P3), right = lane_right(P3);
+            if (!INSIDE) {
+                left = in(side.west) ? P3 : left;
+                right = in(side.east) ? P3 : right;
+            }
+            out = __builtin_fmaf(1.0f - w, P3, 0.25f * w * ((up + down) + left + right));
+        }
+        float fill = 0.25f * (N3 + N2);
+        asm("" : "+v"(out), "+v"(fill));  // both computed, then chosen: no branch
+        out = in(O4 | O3) ? out : fill;
+
+        H2 = H1; H1 = Ha; S1 = S0;
+        D2 = D1; Y2 = Y1;
+        W2 = W1; X3 = X2; B3 = B2; O4 = O3; O3 = O2;
+        UR3 = UR2; UL3 = UL2;
+        P4 = P3; P3 = P2;
+        N3 = N2; N2 = N1; M1 = Mc;
+        return out;
+    }
+};
+
+// A segment of R rows through one round or, with PAIR, through two: the second
+// takes the rows of the first three steps later, so the corners between the
+// two never leave the wave.
+template <bool INIT, bool PAIR, bool INSIDE, int R>
 __device__ __forceinline__ void recon_rows(int nx, int ny, int J0, int I0, const float *__restrict__ Hm,
                                            const uint8_t *__restrict__ land, const float *__restrict__ Hin, float w,
                                            float *__restrict__ Hout)
 {
-    constexpr int NS = R + 6;  // steps: three warm-up rows below, three above
+    constexpr int H = halo(PAIR), NS = R + 2 * H;  // steps: H warm-up rows below, H above
     const int lane = threadIdx.x & 63, I = I0 + lane;
     const uint32_t Ic = (uint32_t)(INSIDE ? I : min(max(I, 0), nx));
     const uint32_t ic = (uint32_t)(INSIDE ? I : min(max(I, 0), nx - 1));
@@ -144,9 +219,8 @@ __device__ __forceinline__ void recon_rows(int nx, int ny, int J0, int I0, const
     const Plane corners_in(Hin, nxc * 4u, (uint32_t)ny + 1), corners_out(Hout, nxc * 4u, (uint32_t)ny + 1);
     const Plane cells(Hm, (uint32_t)nx * 4u, (uint32_t)ny), mask(land, (uint32_t)nx, (uint32_t)ny);
     const Mask cols = INSIDE ? ~(Mask)0 : __builtin_amdgcn_ballot_w64(I >= 0 && I < nx);
-    const Mask west = __builtin_amdgcn_ballot_w64(I <= 0), east = __builtin_amdgcn_ballot_w64(I >= nx);
-    const float wq = 0.25f * w, wp = 1.0f - w;
-    const int a0 = J0 - 3;
+    const SideLanes side{__builtin_amdgcn_ballot_w64(I <= 0), __builtin_amdgcn_ballot_w64(I >= nx)};
+    const int a0 = J0 - H;
 
     // every load of the segment first (clamped rows: always valid
     // addresses), so the wave waits for memory once, not once per row; a row's
@@ -173,95 +247,65 @@ __device__ __forceinline__ void recon_rows(int nx, int ny, int J0, int I0, const
 #pragma unroll
     for (int k = 0; k < NS; ++k) asm volatile("" : "+v"(Hb[k]), "+v"(Mb[k]), "+v"(Lb[k]));
 
-    // pipeline registers; names give the row relative to the newest corner row a
-    float H1 = 0.f, H2 = 0.f, S1 = 0.f;        // corners a-1, a-2; sum of corner a-1 and its right neighbour
-    float D2 = 0.f, Y2 = 0.f;                  // misfit of cell row a-2 (0 off the water); its difference to row a-3
-    Mask W2 = 0;                               // water flags of cell row a-2
-    Mask X3 = 0, B3 = 0, O3 = 0, O4 = 0;       // rows a-3, a-4: one, both, any of a cell and its left neighbour water
-    float UR3 = 0.f, UL3 = 0.f;                // cell row a-3: estimates at its upper corners
-    float P3 = 0.f, P4 = 0.f;                  // corrected corners of rows a-3, a-4
-    float M1 = 0.f, N2 = 0.f, N3 = 0.f;        // cell values, row a-2; sum with the left neighbour, rows a-3, a-4
+    const auto water = [&](int k) -> Mask {
+        const int j = a0 + k - 1;
+        return (INSIDE || (j >= 0 && j < ny)) ? cols & __builtin_amdgcn_ballot_w64(Lb[k] == 0) : 0;
+    };
+    Round<INIT, INSIDE> first;
+    Round<false, INSIDE> second;
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
-        const int a = a0 + k;
-        const float Ha = Hb[k], Mc = Mb[k];
-
-        // misfit of cell row a-1
-        const Mask W1 = (INSIDE || (a - 1 >= 0 && a - 1 < ny)) ? cols & __builtin_amdgcn_ballot_w64(Lb[k] == 0) : 0;
-        const float S0 = lane_right(Ha) + Ha;
-        const float misfit = INIT ? Mc : __builtin_fmaf(-0.25f, S1 + S0, Mc);
-        const float D1 = in(W1) ? misfit : 0.f;
-
-        // slopes and corner estimates of cell row a-2; all 0 off the water
-        const float Dr = lane_right(D2);
-        const float dx = difference(W2 & (W2 >> 1), Dr, D2), Y1 = difference(W2 & W1, D1, D2);
-        const float sx = 0.5f * minmod2(lane_left(dx), dx), sy = 0.5f * minmod2(Y2, Y1);
-        const float U = D2 + sy, L = D2 - sy;
-        const float UR2 = U + sx, UL2 = U - sx, DR2 = L + sx, DL2 = L - sx;
-
-        // corrected corner row a-2: the mean over the water cells among
-        // (a-3, I-1), (a-3, I), (a-2, I-1), (a-2, I).  Cells off the water add
-        // 0; the number of water cells is summed bit by bit in the masks
-        const Mask W2l = W2 << 1, X2 = W2 ^ W2l, B2 = W2 & W2l, O2 = W2 | W2l;
-        const Mask odd = X3 ^ X2, two = B3 ^ B2 ^ (X3 & X2), four = B3 & B2;
-        const float acc = lane_left(UR3) + UL3 + (lane_left(DR2) + DL2);
-        float share = in(four) ? 0.25f : 1.0f;
-        share = in(two) ? 0.5f : share;
-        share = in(two & odd) ? 1.0f / 3.0f : share;
-        const float P2 = INIT ? acc * share : __builtin_fmaf(acc, share, H2);
-
-        // output row Y = a-3 (the first six steps only fill the pipeline)
-        const int Y = a - 3;
-        const float N1 = lane_left(M1) + M1;
-        if (k >= 6) {
-            float out = P3;
-            if (!INIT) {
-                const float up = (INSIDE || Y < ny) ? P2 : P3, down = (INSIDE || Y > 0) ? P4 : P3;
-                float left = lane_left(P3), right = lane_right(P3);
-                if (!INSIDE) {
-                    left = in(west) ? P3 : left;
-                    right = in(east) ? P3 : right;
-                }
-                out = __builtin_fmaf(wp, P3, wq * ((up + down) + left + right));
-            }
-            float fill = 0.25f * (N3 + N2);
-            asm("" : "+v"(out), "+v"(fill));  // both computed, then chosen: no branch
-            out = in(O4 | O3) ? out : fill;
-            if (lane >= 3 && lane < 3 + RSTRIP && (INSIDE || (I <= nx && Y <= ny))) 
-                corners_out.put(Y, (uint32_t)I, out);
-        }
-
-        H2 = H1; H1 = Ha; S1 = S0;
-        D2 = D1; Y2 = Y1;
-        W2 = W1; X3 = X2; B3 = B2; O4 = O3; O3 = O2;
-        UR3 = UR2; UL3 = UL2;
-        P4 = P3; P3 = P2;
-        N3 = N2; N2 = N1; M1 = Mc;
+        float out = first.next(a0 + k, ny, side, w, Hb[k], Mb[k], water(k));
+        if (PAIR && k >= 6) out = second.next(a0 + k - 3, ny, side, w, out, Mb[k - 3], water(k - 3));
+        const int Y = a0 + k - H;
+        if (k >= 2 * H && lane >= H && lane < H + strip(PAIR) && (INSIDE || (I <= nx && Y <= ny)))
+            corners_out.put(Y, (uint32_t)I, out);
     }
 }
 
-template <bool INIT, int R>
+template <bool INIT, bool PAIR, int R>
 __global__ __launch_bounds__(256) void recon_round_kernel(int nx, int ny, int nsx, int nitems,
                                                           const float *__restrict__ Hm,
                                                           const uint8_t *__restrict__ land,
                                                           const float *__restrict__ Hin, float w,
                                                           float *__restrict__ Hout)
 {
+    constexpr int H = halo(PAIR);
     const int item = wave_item();
     if (item >= nitems) return;  // whole waves leave together
-    const int seg = item / nsx, J0 = seg * R, I0 = (item - seg * nsx) * RSTRIP - 3;
-    if (I0 >= 0 && I0 + 63 < nx && J0 >= 4 && J0 + R + 1 < ny)
-        recon_rows<INIT, true, R>(nx, ny, J0, I0, Hm, land, Hin, w, Hout);
+    const int seg = item / nsx, J0 = seg * R, I0 = (item - seg * nsx) * strip(PAIR) - H;
+    if (I0 >= 0 && I0 + 63 < nx && J0 > H && J0 + R + H - 2 < ny)
+        recon_rows<INIT, PAIR, true, R>(nx, ny, J0, I0, Hm, land, Hin, w, Hout);
     else
-        recon_rows<INIT, false, R>(nx, ny, J0, I0, Hm, land, Hin, w, Hout);
+        recon_rows<INIT, PAIR, false, R>(nx, ny, J0, I0, Hm, land, Hin, w, Hout);
 }
 
-template <bool INIT>
-hipError_t launch_recon_round(int R, unsigned blocks, hipStream_t s, int nx, int ny, int nsx, int items,
-                              const float *Hm, const uint8_t *land, const float *Hin, float w, float *Hout)
+int64_t div_up(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// four items to a block; a second grid dimension where the threads of one
+// would leave 32 bits
+dim3 item_grid(int64_t items)
 {
-    auto *kernel = R == 4 ? recon_round_kernel<INIT, 4> : recon_round_kernel<INIT, 8>;
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, nx, ny, nsx, items, Hm, land, Hin, w, Hout);
+    const int64_t blocks = div_up(items, 4), x = std::min<int64_t>(blocks, 1 << 20);
+    return dim3((unsigned)x, (unsigned)div_up(blocks, x));
+}
+
+template <bool INIT, bool PAIR>
+hipError_t launch_recon(hipStream_t s, int nx, int ny, const float *Hm, const uint8_t *land, const float *Hin, float w,
+                        float *Hout)
+{
+    const int nsx = (nx + 1 + strip(PAIR) - 1) / strip(PAIR);
+    // rows per segment, by the waves that 8 would give: 4 below 1.5 a SIMD (a
+    // wave's rows are a serial chain), 16 from 12 a SIMD (fewer warm-up rows).
+    // Microseconds a round of a pair with 4, 8 and 16 rows: 250 x 130 2.8, 3.5
+    // and 5.0; 1202 x 602 4.6, 4.4 and 5.1; 2600 x 900 8.9, 7.5 and 7.9; 4000
+    // x 2400 25.6, 18.5 and 17.4.  A round alone is never faster with 16 than 8.
+    const int64_t waves = nsx * div_up((int64_t)ny + 1, 8);
+    const int R = waves < 1536 ? 4 : PAIR && waves >= 12288 ? 16 : 8;
+    const int64_t items = (int64_t)nsx * ((ny + 1 + R - 1) / R);
+    auto *kernel = R == 4 ? recon_round_kernel<INIT, PAIR, 4> : R == 8 ? recon_round_kernel<INIT, PAIR, 8>
+                 : recon_round_kernel<INIT, PAIR, PAIR ? 16 : 8>;
+    hipLaunchKernelGGL(kernel, item_grid(items), dim3(256), 0, s, nx, ny, nsx, (int)items, Hm, land, Hin, w, Hout);
     return hipGetLastError();
 }
 
@@ -576,16 +620,6 @@ int hip_error(hipError_t e, const char *what)
     return set_error(SWE_E_HIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
-int64_t div_up(int64_t a, int64_t b) { return (a + b - 1) / b; }
-
-// four items to a block; a second grid dimension where the threads of one
-// would leave 32 bits
-dim3 item_grid(int64_t items)
-{
-    const int64_t blocks = div_up(items, 4), x = std::min<int64_t>(blocks, 1 << 20);
-    return dim3((unsigned)x, (unsigned)div_up(blocks, x));
-}
-
 // Calls launch(first field, items) until all fields and, with the first of
 // them, the corners are done: one launch unless the number of work items
 // would leave 32 bits.
@@ -617,27 +651,18 @@ extern "C" int swe_reconstruct_bathymetry(int32_t nx, int32_t ny, const float *H
     if (iters > 0 && !scratch) return set_error(SWE_E_ARG, "scratch is required when iters > 0");
     if (!(smooth >= 0.0f && smooth <= 1.0f)) return set_error(SWE_E_ARG, "smooth must be in [0, 1]");
     hipStream_t s = (hipStream_t)hip_stream;
-    // rows per segment: 8, or 4 while 8 would give a SIMD fewer than two waves
-    // (six warm-up rows a segment; microseconds a round with 4 and 8 rows:
-    // 500 x 1000 4.8 and 5.4, 1202 x 602 5.5 and 5.6, 2600 x 900 8.8 and 7.9;
-    // 12 and more are slower at every size)
-    const int nsx = (nx + 1 + RSTRIP - 1) / RSTRIP;
-    const int R = (int64_t)nsx * ((ny + 1 + 7) / 8) >= 2048 ? 8 : 4;
-    const int nsy = (ny + 1 + R - 1) / R;
-    const int64_t items = (int64_t)nsx * nsy;
-    if (items > INT32_MAX / 2) return set_error(SWE_E_ARG, "domain too large");
-    const unsigned blocks = (unsigned)((items + 3) / 4);
-    // round k writes Hc when iters - k is even, so the last round ends in Hc
-    float *buf[2] = {Hc, scratch};
-    float *cur = buf[iters & 1];
-    hipError_t e = launch_recon_round<true>(R, blocks, s, nx, ny, nsx, (int)items, Hm, land, nullptr, smooth, cur);
-    if (e != hipSuccess) return hip_error(e, "recon_round_kernel<init>");
-    for (int k = 1; k <= iters; ++k) {
-        float *nxt = buf[(iters - k) & 1];
-        e = launch_recon_round<false>(R, blocks, s, nx, ny, nsx, (int)items, Hm, land, cur, smooth, nxt);
-        if (e != hipSuccess) return hip_error(e, "recon_round_kernel");
+    // the launches of two rounds each end in Hc; the first takes the initial
+    // guess alone when the number of rounds is even
+    int launches = iters / 2 + 1, k = 0;
+    float *buf[2] = {Hc, scratch}, *cur = buf[(launches - 1) & 1];
+    hipError_t e = (iters & 1) ? launch_recon<true, true>(s, nx, ny, Hm, land, nullptr, smooth, cur)
+                               : launch_recon<true, false>(s, nx, ny, Hm, land, nullptr, smooth, cur);
+    while (e == hipSuccess && ++k < launches) {
+        float *nxt = buf[(launches - 1 - k) & 1];
+        e = launch_recon<false, true>(s, nx, ny, Hm, land, cur, smooth, nxt);
         cur = nxt;
     }
+    if (e != hipSuccess) return hip_error(e, "recon_round_kernel");
     return SWE_OK;
 }
 

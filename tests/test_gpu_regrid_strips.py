@@ -75,6 +75,22 @@ def test_corner_depths_at_strip_edges(swe, nx, ny, land_on):  # noqa: F811
         assert np.abs(got - ref).max() <= RECON_TOL * np.abs(Hm).max()
 
 
+def test_corner_depths_of_many_segments(swe):  # noqa: F811
+    """The longest segments, which only large grids take: windows of rows
+    against the oracle, which reaches 3 k + 2 cells in k rounds."""
+    nx, ny, k = 60, 49157, 3
+    rng = np.random.default_rng(8)
+    Hm = rng.uniform(5.0, 80.0, (ny, nx)).astype(np.float32)
+    land = (rng.uniform(size=(ny, nx)) < 0.3).astype(np.uint8)
+    print(nx, ny, k, flush=True)
+    got = _host(swe.reconstruct_bathymetry(_cuda(Hm), _cuda(land), iters=k))
+    for lo in (0, 1007, 24999, ny - 100):
+        a, b = max(0, lo - 12), min(ny, lo + 112)
+        ref = P.reconstruct_bathymetry(Hm[a:b], land[a:b], iters=k)
+        end = ny + 1 if b == ny else lo + 100
+        assert np.abs(got[lo:end] - ref[lo - a:end - a]).max() <= RECON_TOL * np.abs(Hm).max()
+
+
 def test_land_values_stay_behind_the_mask(swe):  # noqa: F811
     """NaN and infinities on land reach no water cell."""
     nx, ny = 130, 22
