@@ -368,10 +368,17 @@ void drop_graphs(swe_domain *d)
     d->graph_objs.clear();
 }
 
+int have_pinned_ctrl(swe_domain *d)
+{
+    if (!d->pinned_ctrl) HIP_TRY(hipHostMalloc((void **)&d->pinned_ctrl, sizeof(Ctrl), hipHostMallocDefault));
+    return SWE_OK;
+}
+
 // the copy of the control block to pinned_ctrl, enqueued
 int start_ctrl(swe_domain *d)
 {
-    if (!d->pinned_ctrl) HIP_TRY(hipHostMalloc((void **)&d->pinned_ctrl, sizeof(Ctrl), hipHostMallocDefault));
+    const int rc = have_pinned_ctrl(d);
+    if (rc) return rc;
     HIP_TRY(hipMemcpyAsync(d->pinned_ctrl, d->dom.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, d->stream));
     return SWE_OK;
 }
@@ -406,6 +413,22 @@ bool is_pageable(const void *p)
         return true;
     }
     return a.type == hipMemoryTypeUnregistered;
+}
+
+// the GPU in whose own memory `bytes` bytes at p lie, or -1 (other memory, or
+// an allocation that ends before them)
+int device_of(void *p, size_t bytes)
+{
+    hipPointerAttribute_t a;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess ||
+        (a.type == hipMemoryTypeDevice && hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess)) {
+        (void)hipGetLastError();
+        return -1;
+    }
+    if (a.type != hipMemoryTypeDevice || (uintptr_t)p - (uintptr_t)base + bytes > size) return -1;
+    return a.device;
 }
 
 }  // namespace
@@ -787,6 +810,18 @@ int swe_read_state(swe_domain *d, float *eta, float *hu, float *hv, double *t, d
     float *to[3];
     const float *from[3];
     int staged = 0;
+    StateRead q{};
+    q.ctrl = d->dom.ctrl;
+    q.nx = nx; q.ny = ny; q.pitch = d->dom.pitch;
+    // planes in the memory of the domain's own GPU go by one kernel; pinned
+    // host memory, other GPUs' and planes that overlap one another by copies
+    // in order
+    const size_t planeb = (size_t)nx * ny * sizeof(float);
+    const auto apart = [&](int a, int b) {
+        const uintptr_t x = (uintptr_t)dst[a], y = (uintptr_t)dst[b];
+        return !dst[a] || !dst[b] || x + planeb <= y || y + planeb <= x;
+    };
+    const int own = apart(0, 1) && apart(0, 2) && apart(1, 2) ? device_of(d->ws, 1) : -1;
     for (int k = 0; k < 3; ++k) {
         if (!dst[k]) continue;
         if (is_pageable(dst[k])) {
@@ -794,11 +829,20 @@ int swe_read_state(swe_domain *d, float *eta, float *hu, float *hv, double *t, d
             from[staged++] = src[k];
             continue;
         }
+        if (own >= 0 && device_of(dst[k], planeb) == own && (uintptr_t)dst[k] % sizeof(float) == 0) {
+            q.src[q.planes] = src[k];
+            q.dst[q.planes++] = dst[k];
+            continue;
+        }
         HIP_TRY(hipMemcpy2DAsync(dst[k], (size_t)nx * sizeof(float), src[k], (size_t)d->dom.pitch * sizeof(float),
                                  (size_t)nx * sizeof(float), (size_t)ny, hipMemcpyDefault, d->stream));
     }
-    int rc = start_ctrl(d);
+    int rc = q.planes > 0 ? have_pinned_ctrl(d) : start_ctrl(d);
     if (rc) return rc;
+    if (q.planes > 0) {
+        q.ctrl_out = d->pinned_ctrl;
+        HIP_TRY(launch_read_state(q, d->stream));
+    }
     if (staged > 0) HIP_TRY(read_planes(d->stream, staged, to, from, d->dom.pitch, nx, ny));
     else HIP_TRY(hipStreamSynchronize(d->stream));
     const Ctrl &c = *d->pinned_ctrl;

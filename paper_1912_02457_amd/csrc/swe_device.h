@@ -57,6 +57,16 @@ struct Ctrl {
     uint32_t wslot[2][kCflSlots][kCflStride];
 };
 
+// A read of state planes (their cell (0, 0) in the frames) into dense device
+// planes, and of the control block into pinned host memory.
+struct StateRead {
+    const float *src[3];
+    float *dst[3];
+    const Ctrl *ctrl;
+    Ctrl *ctrl_out;
+    int nx, ny, pitch, planes;
+};
+
 // host-side text of the error flags
 inline const char *flag_message(uint32_t flags)
 {

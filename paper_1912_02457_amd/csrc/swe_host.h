@@ -24,6 +24,7 @@ hipError_t launch_frame_state(const Dom &d, int parity, hipStream_t s);
 hipError_t launch_set_t_end(Ctrl *c, double te, hipStream_t s);
 hipError_t launch_policy_reset(Ctrl *c, int parity, hipStream_t s);
 hipError_t launch_diagnostics(const Dom &d, hipStream_t s);
+hipError_t launch_read_state(const StateRead &q, hipStream_t s);
 int stage_waves_per_simd(int stage, bool proj, bool comp);
 
 int set_error(int code, const std::string &msg);  // records the message for swe_last_error
