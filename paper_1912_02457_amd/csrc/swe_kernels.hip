@@ -193,8 +193,31 @@ __device__ __forceinline__ void time_weights(int n, const double *ts, double tau
     s = (tau - ta) / (tb - ta);
 }
 
-// wave-wide maximum of a float (every lane gets the result)
-__device__ __forceinline__ float wave_max(float v)
+// Wave-wide maximum of unsigned numbers, the same scalar in every lane.  Steps
+// within rows of 16 lanes, then the last lane of a row (and of the lower half)
+// to those above; a lane without a source takes 0.  Cross-lane moves of the
+// vector unit: six dependent trips through LDS (__shfl_xor) took 0.2 us, at
+// the start of every stage 1 and the end of every stage 2 (us a step with them
+// and without: 128 x 128 bump 9.62 and 9.26, 331 x 217 channel 12.2 and 12.0,
+// 777 x 333 bay 14.5 and 14.2).
+template <int CTRL>
+__device__ __forceinline__ uint32_t max_step(uint32_t v)
+{
+    return max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t v)
+{
+    v = max_step<0x111>(v);  // row_shr:1, 2, 4, 8
+    v = max_step<0x112>(v);
+    v = max_step<0x114>(v);
+    v = max_step<0x118>(v);
+    v = max_step<0x142>(v);  // row_bcast:15, 31
+    v = max_step<0x143>(v);
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
+}
+
+// wave-wide maximum of a float that may be anything (NaN is passed over)
+__device__ __forceinline__ float wave_max_any(float v)
 {
     for (int off = kWave / 2; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, kWave));
     return v;
@@ -203,9 +226,7 @@ __device__ __forceinline__ float wave_max(float v)
 // CFL accumulator of one parity: maximum over the slots (all lanes get it)
 __device__ __forceinline__ uint32_t read_wmax(const Ctrl *c, int parity, int lane)
 {
-    uint32_t v = c->wslot[parity][lane & (kCflSlots - 1)][0];
-    for (int off = kWave / 2; off > 0; off >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, off, kWave));
-    return v;
+    return wave_max(c->wslot[parity][lane & (kCflSlots - 1)][0]);
 }
 
 
@@ -1195,10 +1216,11 @@ __device__ __forceinline__ void process_tile(const D &d, DomK *dk, FrsTable &ft,
     run_tile<STAGE, PROJ, W10, COMP>(d, dk, ft, c, start, y0, y1, wmax_loc, bad);
 
     if (STAGE == 2) {
-        wmax_loc = wave_max(wmax_loc);
+        // at least +0 and no NaN, so its bits are ordered as it is
+        const uint32_t wbits = wave_max(__float_as_uint(wmax_loc));
         const uint32_t fl = (bad.nonfinite ? 1u : 0u) | (bad.negative ? 2u : 0u);
         if (lane == 0) {
-            atomicMax(&d.ctrl->wslot[parity ^ 1][tile & (kCflSlots - 1)][0], __float_as_uint(wmax_loc));
+            atomicMax(&d.ctrl->wslot[parity ^ 1][tile & (kCflSlots - 1)][0], wbits);
             if (fl) atomicOr(&d.ctrl->flags, fl);
         }
     }
@@ -1289,7 +1311,7 @@ __global__ void cfl_kernel(Dom d, int slot)
             if (h < -d.kappa) bad |= 2;
         }
     }
-    w = wave_max(w);
+    w = wave_max_any(w);
     const uint32_t fl = (__ballot(bad & 1) ? 1u : 0u) | (__ballot(bad & 2) ? 2u : 0u);
     if ((threadIdx.x & (kWave - 1)) == 0) {
         int k = (blockIdx.x + blockIdx.y * gridDim.x + (threadIdx.x / kWave)) & (kCflSlots - 1);
