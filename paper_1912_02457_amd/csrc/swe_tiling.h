@@ -102,6 +102,12 @@ inline double launch_rows(long n1, double c1, long n2, double c2, int ncu, int r
     }
 }
 
+// No launch of these blocks ends before this: the chip full until the end.
+inline double launch_rows_least(long n1, double c1, long n2, double c2, int ncu, int room)
+{
+    return ((double)n1 * c1 + (double)n2 * c2) * (1.0 + kSharing * (room - 1)) / ((double)ncu * room);
+}
+
 // The tiling of one stage kernel on a chip of `cus` CUs where its registers
 // allow `waves_per_simd` waves.
 inline Tiling default_tiling(int nx, int ny, int cus, int waves_per_simd)
@@ -115,8 +121,11 @@ inline Tiling default_tiling(int nx, int ny, int cus, int waves_per_simd)
     Tiling best = make_tiling(nx, ny, 1);
     double best_t = INFINITY;
     auto consider = [&](const Tiling &T) {
-        const double t = launch_rows(T.nblk1, T.by + kBandStart, T.nblocks - T.nblk1, T.by2 + kBandStart, cus, room) *
-                         (T.nrb1 == T.nrb && T.by > 1 ? kOneHeight : 1.0);
+        const long n1 = T.nblk1, n2 = T.nblocks - T.nblk1;
+        const double c1 = T.by + kBandStart, c2 = T.by2 + kBandStart;
+        const double uneven = T.nrb1 == T.nrb && T.by > 1 ? kOneHeight : 1.0;
+        if (launch_rows_least(n1, c1, n2, c2, cus, room) * uneven >= best_t) return;
+        const double t = launch_rows(n1, c1, n2, c2, cus, room) * uneven;
         if (t < best_t) { best_t = t; best = T; }
     };
     for (int by : heights) {
@@ -165,10 +174,12 @@ EnsBands ensemble_bands(const Shapes &shapes, int rows_per_wave, int cus)
             n1 += T.ntiles1;
             n2 += T.ntiles - T.ntiles1;
         }
-        const double start = kBandStart + kEnsembleStart;
-        const double t = launch_rows((n1 + kWavesPerBlock - 1) / kWavesPerBlock, b.by + start,
-                                     (n2 + kWavesPerBlock - 1) / kWavesPerBlock, b.by2 + start, cus, room) *
-                         (n2 == 0 && b.by > 1 ? kOneHeight : 1.0);
+        const double c1 = b.by + kBandStart + kEnsembleStart, c2 = b.by2 + kBandStart + kEnsembleStart;
+        const double uneven = n2 == 0 && b.by > 1 ? kOneHeight : 1.0;
+        n1 = (n1 + kWavesPerBlock - 1) / kWavesPerBlock;
+        n2 = (n2 + kWavesPerBlock - 1) / kWavesPerBlock;
+        if (launch_rows_least(n1, c1, n2, c2, cus, room) * uneven >= best_t) return;
+        const double t = launch_rows(n1, c1, n2, c2, cus, room) * uneven;
         if (t < best_t) { best_t = t; best = b; }
     };
     for (int k = 0; k < nh; ++k) {
