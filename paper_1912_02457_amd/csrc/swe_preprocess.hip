@@ -319,8 +319,9 @@ hipError_t launch_recon(hipStream_t s, int nx, int ny, const float *Hm, const ui
 // those along y in registers, and holds the water flags of a row as one
 // 64-bit scalar.  (Before, a thread loaded a cell's flags, waited, then loaded
 // the neighbours those flags asked for, one cell at a time.)  2600 x 900 with
-// three fields, microseconds before and now: erosion 24 and 13, refinement 77 and 33,
-// coarsening 14 and 9.4 (6.0, 6.0 and 4.8 TB/s).  Cells and corners of one call
+// three fields, microseconds before and now: erosion 24 and 13 to 18 (by what
+// the caches hold), refinement 77 and 33, coarsening 14 and 9.4 (6.0, 6.0 and
+// 4.8 TB/s).  Cells and corners of one call
 // share a launch.  2 or 8 rows to a wave give the same.
 //
 // A vector access of several elements states the alignment of one element:
