@@ -168,7 +168,15 @@ __device__ __forceinline__ double lane_value(double v, int k)
 // record, a step of the 1024 x 1024 beach took 112 us with it and takes 47
 // with this search, and a 331 x 217 channel under 25 snapshots of gridded
 // wind 19.6 and 16.6 us.)
-__device__ __forceinline__ void time_weights(int n, const double *ts, double tau, int &k, double &s)
+// `early`: the lane's entry of a table of up to 63 times, loaded beforehand
+// (first_times), or null.
+__device__ __forceinline__ double first_times(int n, const double *ts)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    return ts[min(lane, n - 1)];
+}
+__device__ __forceinline__ void time_weights(int n, const double *ts, double tau, int &k, double &s,
+                                             const double *early = nullptr)
 {
     k = 0;
     s = 0.0;
@@ -182,8 +190,7 @@ __device__ __forceinline__ void time_weights(int n, const double *ts, double tau
         base += (cnt > 0 ? cnt - 1 : 0) * stride;
         len = min(stride, n - base);
     }
-    const int at = min(base + lane, n - 1);
-    const double t = ts[at];
+    const double t = early && n < kWave ? *early : ts[min(base + lane, n - 1)];
     const int cnt = __popcll(__builtin_amdgcn_ballot_w64(lane < len && t <= tau));
     const int a = cnt > 0 ? cnt - 1 : 0;  // lane of that entry
     if (base + a >= n - 1) { k = n - 2; s = 1.0; return; }
@@ -230,14 +237,39 @@ __device__ __forceinline__ uint32_t read_wmax(const Ctrl *c, int parity, int lan
 }
 
 
+// What the forcing of a tile needs whatever its time, issued with its first
+// rows instead of after the time step is known, one more wait for memory at the
+// head of every wave: the first snapshot of the uniform wind and the times of
+// the tables (us a step before and now: 128 x 128 bump 9.3 and 9.1, 512 x 512
+// 14.6 and 14.0, 331 x 217 channel 12.0 and 11.7, 777 x 333 bay 14.2 and 13.8,
+// beach 38.5 and 38.1).
+struct WindStart {
+    float x, y;
+    double t, t10;
+};
 template <class D>
-__device__ __forceinline__ void wind_at(const D &d, double tau, float &wx, float &wy)
+__device__ __forceinline__ WindStart load_wind(const D &d)
+{
+    WindStart w{0.f, 0.f, 0.0, 0.0};
+    if (d.nw > 0) {
+        w.x = d.wind[0];
+        w.y = d.wind[1];
+        if (d.nw > 1) w.t = first_times(d.nw, d.wind_t);
+    }
+    if (d.w10n > 1) w.t10 = first_times(d.w10n, d.w10_t);
+    return w;
+}
+
+template <class D>
+__device__ __forceinline__ void wind_at(const D &d, double tau, const WindStart &w, float &wx, float &wy)
 {
     if (d.nw <= 0) { wx = wy = 0.f; return; }
-    int k; double s;
-    time_weights(d.nw, d.wind_t, tau, k, s);
-    double ax = d.wind[2 * k], ay = d.wind[2 * k + 1];
+    double ax = w.x, ay = w.y;
     if (d.nw > 1) {
+        int k; double s;
+        time_weights(d.nw, d.wind_t, tau, k, s, &w.t);
+        ax = d.wind[2 * k];
+        ay = d.wind[2 * k + 1];
         ax = (1.0 - s) * ax + s * (double)d.wind[2 * k + 2];
         ay = (1.0 - s) * ay + s * (double)d.wind[2 * k + 3];
     }
@@ -1173,18 +1205,19 @@ __device__ __forceinline__ void process_tile(const D &d, DomK *dk, FrsTable &ft,
     c.out = __builtin_amdgcn_ballot_w64(c.out_lane);
     c.xneed = c.out | left_in(c.out) | right_in(c.out);
     const TileStart start = load_start<STAGE, PROJ>(d, c.i, y0 - kHalo);
+    const WindStart wind = load_wind(d);
 
     const StepTime st = STAGE == 1 ? step_time(d, parity, dt_fixed, lane) : step_published(d, parity);
     if (STAGE == 1 && advance) advance_ctrl(d.ctrl, st, parity, lane);
     if (st.skip) return;
     const double tau = STAGE == 1 ? st.tn : st.tn + st.dtd;
     c.dt = (float)st.dtd;
-    wind_at(d, tau, c.wx, c.wy);
+    wind_at(d, tau, wind, c.wx, c.wy);
     c.wk = 0;
     c.ws = 0.f;
     if (d.w10n > 0) {
         double s;
-        time_weights(d.w10n, d.w10_t, tau, c.wk, s);
+        time_weights(d.w10n, d.w10_t, tau, c.wk, s, &wind.t10);
         c.ws = (float)s;
     }
 
