@@ -813,15 +813,17 @@ int swe_read_state(swe_domain *d, float *eta, float *hu, float *hv, double *t, d
     StateRead q{};
     q.ctrl = d->dom.ctrl;
     q.nx = nx; q.ny = ny; q.pitch = d->dom.pitch;
-    // planes in the memory of the domain's own GPU go by one kernel; pinned
-    // host memory, other GPUs' and planes that overlap one another by copies
-    // in order
+    // planes in the memory of the domain's own GPU go by one kernel, if that
+    // GPU is the calling thread's (a launch needs it to be, a copy does not);
+    // pinned host memory, other GPUs' and planes that overlap one another by
+    // copies in order
     const size_t planeb = (size_t)nx * ny * sizeof(float);
     const auto apart = [&](int a, int b) {
         const uintptr_t x = (uintptr_t)dst[a], y = (uintptr_t)dst[b];
         return !dst[a] || !dst[b] || x + planeb <= y || y + planeb <= x;
     };
-    const int own = apart(0, 1) && apart(0, 2) && apart(1, 2) ? device_of(d->ws, 1) : -1;
+    int own = apart(0, 1) && apart(0, 2) && apart(1, 2) ? device_of(d->ws, 1) : -1, current = -1;
+    if (hipGetDevice(&current) != hipSuccess || current != own) own = -1;
     for (int k = 0; k < 3; ++k) {
         if (!dst[k]) continue;
         if (is_pageable(dst[k])) {
