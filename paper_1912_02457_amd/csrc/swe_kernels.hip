@@ -923,9 +923,12 @@ __device__ __forceinline__ void finish_row(const Row &A, const F3 &Gs, const F3 
         bad.negative |= stored & __builtin_amdgcn_ballot_w64(h < -d.kappa);
         const float ri = rcp(desing(h, d));
         const float cw = fsqrt(d.g * fmaxf(h, 0.f));
-        // (with square cells the larger speed is taken first: the same value)
+        // with square cells the larger speed is taken first: the same value,
+        // bit for bit, rounding being monotone, as long as the product is
+        // rounded before the sum as in the other form and in cfl_kernel (the
+        // outer fabsf keeps the two from fusing)
         float w;
-        if (likely(d.rdx == d.rdy)) w = (fmaxf(fabsf(un), fabsf(vn)) * fabsf(ri) + cw) * d.rdx;
+        if (likely(d.rdx == d.rdy)) w = (fabsf(fmaxf(fabsf(un), fabsf(vn)) * ri) + cw) * d.rdx;
         else w = fmaxf((fabsf(un * ri) + cw) * d.rdx, (fabsf(vn * ri) + cw) * d.rdy);
         wmax_loc = store ? fmaxf(wmax_loc, w) : wmax_loc;
         bad.nonfinite |= stored & (__builtin_amdgcn_ballot_w64(!isfinite(en)) | __builtin_amdgcn_ballot_w64(!isfinite(un)) |
