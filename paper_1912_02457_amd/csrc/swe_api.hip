@@ -2,16 +2,17 @@
 // workspace layout, uploads, launches, HIP-graph replay of step chunks and
 // kernel timing.  No exception crosses the ABI.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
-#include <mutex>
 #include <map>
 #include <string>
 #include <utility>
 #include <vector>
 
 #include "swe_host.h"
+#include "swe_staging.h"
 #include "swe_tiling.h"
 
 using namespace swe;
@@ -132,32 +133,46 @@ int swe::set_error(int code, const std::string &msg) { return fail(code, msg); }
 
 namespace {
 
-// Copies between pageable host memory and pitched device planes go through one
-// process-wide pinned staging buffer (at most 64 MiB, or one row if that is
-// more; larger arrays go in row chunks): a direct copy would be split by the
-// runtime into row-sized transfers, and a pinned buffer per domain costs 4 ms
-// of page pinning on a domain's first read (1375 x 664 cells; the read itself
-// takes 0.6 ms).  The buffer is held for the whole copy sequence of one call.
-constexpr size_t kStageCap = (size_t)64 << 20;
-std::mutex g_stage_mu;
-char *g_stage = nullptr;
-size_t g_stage_bytes = 0;
+// Copies between pageable host memory and pitched device planes go through a
+// pinned staging buffer (at most 64 MiB, or one row if that is more; larger
+// arrays go in row chunks): a direct copy would be split by the runtime into
+// row-sized transfers, and a pinned buffer per domain costs 4 ms of page
+// pinning on a domain's first read (1375 x 664 cells; the read itself takes
+// 0.6 ms).
+struct PinnedMemory {
+    static char *get(size_t bytes)
+    {
+        void *p = nullptr;
+        if (hipHostMalloc(&p, bytes, hipHostMallocDefault) == hipSuccess) return (char *)p;
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    static void put(char *p) { (void)hipHostFree(p); }
+};
+StagePool<PinnedMemory> g_stage;
+std::atomic<int> g_domains{0};  // the pool is trimmed when the last one goes
 
-// at least `need` bytes; the caller holds g_stage_mu and has no copy in flight
-hipError_t stage_reserve(size_t need)
-{
-    if (g_stage_bytes >= need) return hipSuccess;
-    if (g_stage) (void)hipHostFree(g_stage);
-    g_stage = nullptr;
-    g_stage_bytes = 0;
-    hipError_t e = hipHostMalloc((void **)&g_stage, need, hipHostMallocDefault);
-    if (e == hipSuccess) g_stage_bytes = need;
-    return e;
-}
+// a buffer of the pool for the length of one call
+class Staging {
+public:
+    ~Staging() { g_stage.give(b_); }
+    hipError_t reserve(size_t need)
+    {
+        if (b_.bytes >= need) return hipSuccess;
+        g_stage.give(b_);
+        b_ = g_stage.take(need);
+        return b_.p ? hipSuccess : hipErrorOutOfMemory;
+    }
+    char *data() const { return b_.p; }
+    size_t bytes() const { return b_.bytes; }
+
+private:
+    StageBuffer b_;
+};
 
 class Uploader {
 public:
-    Uploader(hipStream_t s, size_t hint) : lk_(g_stage_mu), s_(s) { hint_ = std::min(hint, kStageCap); }
+    Uploader(hipStream_t s, size_t hint) : s_(s) { hint_ = std::min(hint, kStageCap); }
     ~Uploader()
     {
         if (pending_) (void)hipStreamSynchronize(s_);
@@ -169,13 +184,13 @@ public:
         hipError_t e;
         if ((e = ensure(std::max(rowb, hint_))) != hipSuccess) return e;
         for (int r0 = 0; r0 < h;) {
-            size_t room = g_stage_bytes - used_;
+            size_t room = st_.bytes() - used_;
             if (room < rowb) {
                 if ((e = flush()) != hipSuccess) return e;
-                room = g_stage_bytes;
+                room = st_.bytes();
             }
             const int rows = (int)std::min<size_t>((size_t)(h - r0), room / rowb);
-            char *stg = g_stage + used_;
+            char *stg = st_.data() + used_;
             std::memcpy(stg, src + (size_t)r0 * w, (size_t)rows * rowb);
             e = hipMemcpy2DAsync((char *)dst + (size_t)r0 * dpitch * sizeof(float), (size_t)dpitch * sizeof(float),
                                  stg, rowb, rowb, (size_t)rows, hipMemcpyHostToDevice, s_);
@@ -197,14 +212,14 @@ public:
 private:
     hipError_t ensure(size_t need)
     {
-        if (g_stage_bytes >= need) return hipSuccess;
+        if (st_.bytes() >= need) return hipSuccess;
         if (pending_) {
             hipError_t e = flush();
             if (e != hipSuccess) return e;
         }
-        return stage_reserve(need);
+        return st_.reserve(need);
     }
-    std::unique_lock<std::mutex> lk_;
+    Staging st_;
     hipStream_t s_;
     size_t hint_ = 0, used_ = 0;
     bool pending_ = false;
@@ -216,28 +231,25 @@ private:
 // the host empties the other.
 hipError_t read_planes(hipStream_t s, int n, float *const *dst, const float *const *src, int spitch, int w, int h)
 {
-    // the steps still running on this stream are waited for before the buffer
-    // is taken: other threads' copies do not wait for them too
-    hipError_t e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return e;
-    std::lock_guard<std::mutex> lk(g_stage_mu);
     const size_t rowb = (size_t)w * sizeof(float), planeb = rowb * (size_t)h;
-    e = stage_reserve(std::max(rowb, std::min((size_t)n * planeb, kStageCap)));
+    Staging st;
+    hipError_t e = st.reserve(std::max(rowb, std::min((size_t)n * planeb, kStageCap)));
     if (e != hipSuccess) return e;
+    char *const buf = st.data();
     auto fetch = [&](char *to, int k, int r0, int rows) {
         return hipMemcpy2DAsync(to, rowb, src[k] + (size_t)r0 * spitch, (size_t)spitch * sizeof(float), rowb, (size_t)rows,
                                 hipMemcpyDeviceToHost, s);
     };
-    if ((size_t)n * planeb <= g_stage_bytes) {
-        for (int k = 0; k < n && e == hipSuccess; ++k) e = fetch(g_stage + k * planeb, k, 0, h);
+    if ((size_t)n * planeb <= st.bytes()) {
+        for (int k = 0; k < n && e == hipSuccess; ++k) e = fetch(buf + k * planeb, k, 0, h);
         const hipError_t w_ = hipStreamSynchronize(s);
         if (e == hipSuccess) e = w_;
         if (e != hipSuccess) return e;
-        for (int k = 0; k < n; ++k) std::memcpy(dst[k], g_stage + k * planeb, planeb);
+        for (int k = 0; k < n; ++k) std::memcpy(dst[k], buf + k * planeb, planeb);
         return hipSuccess;
     }
-    const int slots = g_stage_bytes / 2 >= rowb ? 2 : 1;
-    const size_t slotb = g_stage_bytes / slots;
+    const int slots = st.bytes() / 2 >= rowb ? 2 : 1;
+    const size_t slotb = st.bytes() / slots;
     const int rows = (int)std::min<size_t>((size_t)h, slotb / rowb);
     hipEvent_t ev[2] = {nullptr, nullptr};
     for (int q = 0; q < slots && e == hipSuccess; ++q) e = hipEventCreateWithFlags(&ev[q], hipEventDisableTiming);
@@ -246,13 +258,13 @@ hipError_t read_planes(hipStream_t s, int n, float *const *dst, const float *con
         hipError_t x = hipEventSynchronize(ev[c % slots]);
         const int k = c / per, r0 = (c % per) * rows;
         if (x == hipSuccess)
-            std::memcpy(dst[k] + (size_t)r0 * w, g_stage + (size_t)(c % slots) * slotb, (size_t)std::min(rows, h - r0) * rowb);
+            std::memcpy(dst[k] + (size_t)r0 * w, buf + (size_t)(c % slots) * slotb, (size_t)std::min(rows, h - r0) * rowb);
         return x;
     };
     for (int c = 0; c < chunks && e == hipSuccess; ++c) {
         if (c >= slots) e = empty(c - slots);
         const int k = c / per, r0 = (c % per) * rows;
-        if (e == hipSuccess) e = fetch(g_stage + (size_t)(c % slots) * slotb, k, r0, std::min(rows, h - r0));
+        if (e == hipSuccess) e = fetch(buf + (size_t)(c % slots) * slotb, k, r0, std::min(rows, h - r0));
         if (e == hipSuccess) e = hipEventRecord(ev[c % slots], s);
     }
     for (int c = std::max(0, chunks - slots); c < chunks && e == hipSuccess; ++c) e = empty(c);
@@ -583,6 +595,7 @@ int swe_init_domain(const swe_params *p, void *dev_workspace, size_t bytes, void
     if ((e = launch_frame_static(D, s)) != hipSuccess) { delete d; return hip_fail(e, "frames"); }
     if ((r = reset_time_and_cfl(d, 0.0)) || (r = copy_state_to_star(d))) { delete d; return r; }
     if ((e = hipStreamSynchronize(s)) != hipSuccess) { delete d; return hip_fail(e, "init sync"); }
+    g_domains.fetch_add(1);
     *out = d;
     return SWE_OK;
 }
@@ -1240,6 +1253,7 @@ void swe_destroy(swe_domain *d)
     if (d->pinned_ctrl) (void)hipHostFree(d->pinned_ctrl);
     if (d->pinned_state) (void)hipHostFree(d->pinned_state);
     delete d;
+    if (g_domains.fetch_sub(1) == 1) g_stage.trim();
 }
 
 }  // extern "C"
