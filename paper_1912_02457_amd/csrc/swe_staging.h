@@ -20,6 +20,7 @@ namespace swe {
 constexpr size_t kStageCap = (size_t)64 << 20;  // what a call asks for at most (or one row, if that is more)
 constexpr size_t kStageKept = 4 * kStageCap;
 constexpr int kStageSlots = 16;
+constexpr size_t kStageUnit = (size_t)1 << 20;
 
 struct StageBuffer {
     char *p = nullptr;
@@ -32,19 +33,27 @@ template <class Memory>
 class StagePool {
 public:
     // the smallest idle buffer of at least `need` bytes or a new one; p is
-    // nullptr where no memory is to be had
+    // nullptr where no memory is to be had.  A new buffer has at least twice
+    // the bytes of the largest idle one (up to kStageCap) and whole MiB:
+    // calls of ever larger sizes pin memory a few times, not each time (135
+    // sizes from 0.1 to 67 MB one after another: 7 buffers; pinning 11 MB
+    // takes 4 ms)
     StageBuffer take(size_t need)
     {
+        size_t want = need;
         {
             std::lock_guard<std::mutex> lk(mu_);
             int k = -1;
             for (int q = 0; q < n_; ++q)
                 if (idle_[q].bytes >= need && (k < 0 || idle_[q].bytes < idle_[k].bytes)) k = q;
             if (k >= 0) return remove(k);
+            for (int q = 0; q < n_; ++q) want = std::max(want, std::min(2 * idle_[q].bytes, kStageCap));
         }
+        want = (want + kStageUnit - 1) / kStageUnit * kStageUnit;
         StageBuffer b;
-        b.p = Memory::get(need);
-        if (b.p) b.bytes = need;
+        b.p = Memory::get(want);
+        if (!b.p && want > need) b.p = Memory::get(want = need);
+        if (b.p) b.bytes = want;
         return b;
     }
 

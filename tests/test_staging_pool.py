@@ -86,6 +86,19 @@ int main()
         Fake::put(held.begin()->first);
         CHECK(held.empty());
     }
+    {   // ever larger calls pin memory a few times, and little more than they need
+        StagePool<Fake> p;
+        const long g = gets;
+        for (size_t n = 100 * 1000; n <= kStageCap; n += 500 * 1000) {
+            StageBuffer b = p.take(n);
+            CHECK(b.p && b.bytes >= n && b.bytes <= std::max(2 * n, (size_t)2 * MiB));
+            p.give(b);
+        }
+        CHECK(gets - g <= 8 && total() <= kStageKept);
+        p.trim();
+        CHECK(held.size() == 1);
+        Fake::put(held.begin()->first);
+    }
     {   // threads: every buffer is one thread's at a time
         StagePool<Fake> p;
         std::vector<std::thread> ts;
