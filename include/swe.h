@@ -304,9 +304,10 @@ const char *swe_last_error(void);
  * (including swe_read_state) is ordered on the ensemble's stream. */
 typedef struct swe_ensemble swe_ensemble;
 
-/* Device workspace for an ensemble of these members with rows_per_wave rows
- * per tile (0 = default) -- the member table, the work queue and its
- * counters.  Errors: SWE_E_ARG. */
+/* Device workspace for an ensemble of these members with row bands of
+ * rows_per_wave rows (0 = one height or two, chosen by a model of how the
+ * launch fills the chip) -- the member table, the list of work items and
+ * their counts.  Errors: SWE_E_ARG. */
 int swe_ensemble_workspace_bytes(swe_domain *const *members, int32_t n, int32_t rows_per_wave, size_t *bytes);
 
 /* Group n >= 1 ready domains (boundary data set where nested; all with the
@@ -322,8 +323,8 @@ int swe_ensemble_create(swe_domain *const *members, int32_t n, void *dev_workspa
  * Asynchronous. */
 int swe_ensemble_step(swe_ensemble *e, int32_t n_steps);
 
-/* Reports the work decomposition (rows per tile, chunk, work items per
- * stage, blocks of a launch). */
+/* Reports the work decomposition (rows per tile -- of the tall bands, where
+ * there are two heights --, chunk, work items per stage, blocks of a launch). */
 int swe_ensemble_info(swe_ensemble *e, int32_t *rows_per_wave, int32_t *chunk, int64_t *items, int32_t *blocks);
 
 /* HIP-event timing of the two ensemble stage kernels, as swe_stage_times. */

@@ -141,9 +141,10 @@ inline Tiling default_tiling(int nx, int ny, int cus, int waves_per_simd)
     return best;
 }
 
-// The bands of an ensemble's members: `by` rows, the last `tail` bands of each
-// member of by2 rows (0: one height).  The same model over all members at
-// once; rows_per_wave > 0 fixes by.
+// The bands of an ensemble's members: `by` rows, and after them, where tail is
+// not 0, bands of by2 rows: at least `tail` of them in each member, and the
+// rows that whole bands of `by` leave before those.  A member too short for
+// both has one height.
 struct EnsBands {
     int by, by2, tail;
     Tiling of(int nx, int ny) const { return make_tiling_tail(nx, ny, by, by2, by2 * tail); }
@@ -152,9 +153,12 @@ struct EnsBands {
 constexpr double kEnsembleStart = 1.0;  // rows more than kBandStart: the item and its member's fields
 constexpr int kEnsembleRows = 16;       // where the workspace holds no more items than these bands give
 
+// rows_per_wave > 0 is the height of every band; with 0 the same model as
+// above chooses, over all members at once.
 template <class Shapes>  // of (nx, ny) pairs
 EnsBands ensemble_bands(const Shapes &shapes, int rows_per_wave, int cus)
 {
+    if (rows_per_wave) return EnsBands{rows_per_wave, 0, 0};
     static const int heights[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16};
     const int room = 4, nh = sizeof(heights) / sizeof(heights[0]);
     int64_t strips = 0, rows = 0;
@@ -164,7 +168,7 @@ EnsBands ensemble_bands(const Shapes &shapes, int rows_per_wave, int cus)
         rows += n * s.second;
     }
     const int64_t slots = (int64_t)cus * kWavesPerBlock * room;
-    EnsBands best{rows_per_wave ? rows_per_wave : kEnsembleRows, 0, 0};
+    EnsBands best{kEnsembleRows, 0, 0};
     const double per_slot = (double)rows / slots;
     double best_t = INFINITY;
     auto consider = [&](const EnsBands &b) {
@@ -183,11 +187,10 @@ EnsBands ensemble_bands(const Shapes &shapes, int rows_per_wave, int cus)
         if (t < best_t) { best_t = t; best = b; }
     };
     for (int k = 0; k < nh; ++k) {
-        if (rows_per_wave && k > 0) break;
-        const int h = rows_per_wave ? rows_per_wave : heights[k];
+        const int h = heights[k];
         // the best bands hold 0.4 to 3 times a wave slot's share of the rows
-        if (!rows_per_wave && k < nh - 1 && (h > 3.0 * per_slot + 1.0 || h < 0.4 * per_slot - 1.0)) continue;
-        if (!rows_per_wave && k == nh - 1 && best_t < INFINITY && h > 3.0 * per_slot + 1.0) continue;
+        if (k < nh - 1 && (h > 3.0 * per_slot + 1.0 || h < 0.4 * per_slot - 1.0)) continue;
+        if (k == nh - 1 && best_t < INFINITY && h > 3.0 * per_slot + 1.0) continue;
         consider(EnsBands{h, 0, 0});
         for (int by2 = 1; by2 <= 4 && by2 < h; ++by2)
             for (double rounds : {0.25, 0.5, 1.0}) {
