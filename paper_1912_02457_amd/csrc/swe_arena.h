@@ -40,6 +40,22 @@ public:
         }
         return false;
     }
+    // From the end of the arena, if that is free.  What alloc then finds room
+    // for lies where it would lie without this block, so the arena holds as
+    // much as ever once the block is given back.
+    bool alloc_top(size_t bytes, size_t *off)
+    {
+        bytes = arena_align_up(std::max<size_t>(bytes, 1));
+        if (free_.empty()) return false;
+        auto it = std::prev(free_.end());
+        if (it->first + it->second != size_ || it->second < bytes) return false;
+        *off = size_ - bytes;
+        it->second -= bytes;
+        if (it->second == 0) free_.erase(it);
+        used_ += bytes;
+        peak_ = std::max(peak_, used_);
+        return true;
+    }
     void release(size_t off, size_t bytes)
     {
         bytes = arena_align_up(std::max<size_t>(bytes, 1));

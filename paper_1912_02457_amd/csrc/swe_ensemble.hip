@@ -75,13 +75,6 @@ size_t swe::ensemble_bytes_for_shapes(const std::vector<std::pair<int, int>> &sh
         .total;
 }
 
-size_t swe::ensemble_bytes_preferred(const std::vector<std::pair<int, int>> &shapes)
-{
-    int64_t t = 0;  // an item holds at least one row
-    for (const auto &sh : shapes) t += (int64_t)make_tiling(sh.first, sh.second, 1).ntiles;
-    return ens_layout((int)shapes.size(), t).total;
-}
-
 struct swe_ensemble {
     std::vector<swe_domain *> members;
     hipStream_t stream = nullptr;

@@ -31,9 +31,8 @@ int set_error(int code, const std::string &msg);  // records the message for swe
 // A member destroyed while it still belongs to an ensemble: the ensemble
 // drops it and refuses further steps.
 void ensemble_forget(swe_ensemble *e, swe_domain *d);
-// Device workspace of an ensemble whose members have these (nx, ny) shapes:
-// what it needs, and what lets it choose its bands freely.
-size_t ensemble_bytes_preferred(const std::vector<std::pair<int, int>> &shapes);
+// Device workspace that an ensemble whose members have these (nx, ny) shapes
+// cannot do without (bands of one height).
 size_t ensemble_bytes_for_shapes(const std::vector<std::pair<int, int>> &shapes, int rows_per_wave);
 
 struct Layout {

@@ -74,6 +74,11 @@ struct swe_server {
     swe_ensemble *ens = nullptr;
     size_t ens_off = 0, ens_bytes = 0;          // queue block of the current ensemble
     size_t ens_new_off = 0, ens_new_bytes = 0;  // grown block, swapped in at the next rebuild
+    // Room for the bands the launch model would choose, where the arena has it
+    // to spare: at its top, taken when the ensemble is built and given back as
+    // soon as a request needs the space.
+    size_t wide_off = 0, wide_bytes = 0;
+    bool ens_in_wide = false;  // the current ensemble's list lies there
     bool dirty = false;  // the active set changed since the ensemble was built
     CtrlHead *heads = nullptr;  // pinned, one per active slot
     int64_t submitted = 0, admitted = 0, completed = 0, ticks = 0, cell_steps = 0;
@@ -88,6 +93,13 @@ void drop_ensemble(swe_server *s)
         swe_ensemble_destroy(s->ens);
         s->ens = nullptr;
     }
+    s->ens_in_wide = false;
+}
+
+void release_wide(swe_server *s)
+{
+    if (s->wide_bytes) s->arena.release(s->wide_off, s->wide_bytes);
+    s->wide_bytes = 0;
 }
 
 // Copies a request's host inputs so the caller may free them on return.
@@ -165,6 +177,7 @@ std::vector<swe_domain *> active_domains(swe_server *s)
 void release_queue_blocks(swe_server *s)
 {
     drop_ensemble(s);
+    release_wide(s);
     if (s->ens_bytes) s->arena.release(s->ens_off, s->ens_bytes);
     if (s->ens_new_bytes) s->arena.release(s->ens_new_off, s->ens_new_bytes);
     s->ens_bytes = s->ens_new_bytes = 0;
@@ -199,11 +212,33 @@ void push_back_front(swe_server *s, std::unique_ptr<Pending> q)
     s->pending.push_front(std::move(q));
 }
 
+// Gives the spare block back where that makes room for a request (and for the
+// ensemble's list with it, if queue_bytes is not 0).  Steps that read the list
+// there are waited for first, and the next tick builds the ensemble anew.
+int make_room(swe_server *s, size_t bytes, size_t queue_bytes, bool *made)
+{
+    *made = false;
+    if (!s->wide_bytes) return SWE_OK;
+    Arena trial = s->arena;
+    size_t off;
+    trial.release(s->wide_off, s->wide_bytes);
+    if (!trial.alloc(bytes, &off) || (queue_bytes && !trial.alloc(queue_bytes, &off))) return SWE_OK;
+    if (s->ens_in_wide) {
+        SHIP(hipStreamSynchronize(s->stream));
+        drop_ensemble(s);
+        s->dirty = true;
+    }
+    release_wide(s);
+    *made = true;
+    return SWE_OK;
+}
+
 // Admit waiting requests in arrival order while a slot is free and both the
 // request's workspace and the (possibly grown) ensemble queue fit in the
 // arena.  Runs while the current tick's steps execute: nothing the running
 // ensemble uses is touched (a grown queue block is carved beside the old
-// one and swapped in at the next rebuild).
+// one and swapped in at the next rebuild; the spare block at the top of the
+// arena is given back only behind the steps that use it).
 int admit(swe_server *s)
 {
     std::vector<std::pair<int, int>> shapes;
@@ -221,35 +256,38 @@ int admit(swe_server *s)
                 break;
             }
         }
-        size_t off;
-        if (!s->arena.alloc(q->bytes, &off)) {
-            if (s->active.empty()) return refuse_head(s, std::move(q));  // could never start
-            push_back_front(s, std::move(q));
-            break;
-        }
         // the queue size depends only on the members' shapes
         shapes.emplace_back(q->r.params.nx, q->r.params.ny);
         const size_t need = ensemble_bytes_for_shapes(shapes, s->rows);
-        size_t have = s->ens_new_bytes ? s->ens_new_bytes : s->ens_bytes;
-        // room for free choice of the bands, or else for what is needed
-        const size_t most = ensemble_bytes_preferred(shapes);
-        size_t grow_off = 0, grow_bytes = 0;
-        if (most > have) {
-            grow_bytes = align_up(most + most / 2, kAlign);
-            if (!s->arena.alloc(grow_bytes, &grow_off)) grow_bytes = 0;
-        }
-        if (!grow_bytes && need > have) {
+        const size_t have = s->ens_new_bytes ? s->ens_new_bytes : s->ens_bytes;
+        const size_t grow = need > have ? align_up(need, kAlign) : 0;
+        size_t off = 0, grow_off = 0, grow_bytes = 0;
+        const auto carve = [&]() {
+            if (!s->arena.alloc(q->bytes, &off)) return false;
+            if (!grow) return true;
             grow_bytes = align_up(need + need / 2, kAlign);
-            if (!s->arena.alloc(grow_bytes, &grow_off)) {
-                grow_bytes = align_up(need, kAlign);
-                if (!s->arena.alloc(grow_bytes, &grow_off)) {
-                    s->arena.release(off, q->bytes);
-                    shapes.pop_back();
-                    if (s->active.empty()) return refuse_head(s, std::move(q));
-                    push_back_front(s, std::move(q));
-                    break;
-                }
+            if (s->arena.alloc(grow_bytes, &grow_off)) return true;
+            grow_bytes = grow;  // not before the spare block is gone
+            if (!s->wide_bytes && s->arena.alloc(grow_bytes, &grow_off)) return true;
+            grow_bytes = 0;
+            s->arena.release(off, q->bytes);
+            return false;
+        };
+        bool room = carve();
+        if (!room) {
+            bool made;
+            const int rc = make_room(s, q->bytes, grow, &made);
+            if (rc) {
+                push_back_front(s, std::move(q));
+                return rc;
             }
+            room = made && carve();
+        }
+        if (!room) {
+            shapes.pop_back();
+            if (s->active.empty()) return refuse_head(s, std::move(q));  // could never start
+            push_back_front(s, std::move(q));
+            break;
         }
         swe_domain *d = nullptr;
         int rc = start_request(s, q.get(), off, &d);
@@ -296,8 +334,20 @@ int rebuild(swe_server *s)
     }
     if (s->active.empty()) return SWE_OK;
     std::vector<swe_domain *> doms = active_domains(s);
-    int rc = swe_ensemble_create(doms.data(), (int)doms.size(), s->arena_base + s->ens_off, s->ens_bytes, s->stream,
-                                 s->rows, s->chunk, &s->ens);
+    const int n = (int)doms.size();
+    size_t want = 0;
+    int rc = swe_ensemble_workspace_bytes(doms.data(), n, s->rows, &want);
+    if (rc) return rc;
+    if (want <= s->ens_bytes) {
+        release_wide(s);
+    } else if (s->wide_bytes < want) {
+        release_wide(s);
+        if (s->arena.alloc_top(want, &s->wide_off)) s->wide_bytes = arena_align_up(want);
+    }
+    const bool wide = s->wide_bytes >= want && s->wide_bytes > 0;
+    rc = swe_ensemble_create(doms.data(), n, s->arena_base + (wide ? s->wide_off : s->ens_off),
+                             wide ? s->wide_bytes : s->ens_bytes, s->stream, s->rows, s->chunk, &s->ens);
+    s->ens_in_wide = wide && !rc;
     if (rc) return rc;
     return swe_ensemble_use_graphs(s->ens, 0);
 }
