@@ -229,12 +229,14 @@ int swe_diagnostics(swe_domain *d, double *mass, double *energy);
  * non-land cell; swe_last_error() says which.  Synchronises. */
 int swe_status(swe_domain *d);
 
-/* Measures both stage kernels of this domain for rows per tile in {2..64}
+/* Measures both stage kernels of this domain for the tiling in use and the
+ * built-in choice, for rows per tile in {2..64}
  * and, around the fastest, for tails of 1-4-row bands (swe_set_stage_tiling;
  * on a small domain all rows but the first band),
  * then the winner under the other tile orders (a few launches each), times
- * the three fastest candidates again, and keeps the fastest tiling per
- * stage.  Before anything is timed, stage-1 launches run for about 25 ms of
+ * the tiling in use and the three fastest candidates again, and keeps the
+ * fastest per stage, the one in use unless another is faster.  (Bands of one
+ * row are kept as two-row bands whose every row lies in a one-row tail.)  Before anything is timed, stage-1 launches run for about 25 ms of
  * device time so that the clocks have come up.  The state and the
  * control block are saved to host memory first and restored afterwards, so
  * the simulation does not advance.  *rows_per_wave gets stage 1's choice
@@ -257,7 +259,8 @@ int swe_get_tiling(swe_domain *d, int32_t stage, int32_t *rows_per_wave, int32_t
 /* Tiling of one stage kernel (1 or 2) with two band heights: bands of
  * rows_per_wave rows (>= 1) from the top, and when 0 < tail_rows_per_wave <
  * rows_per_wave, the last rows -- at least tail_rows of them, 0 < tail_rows <
- * ny, with at least one band of rows_per_wave rows before them -- in bands of
+ * ny, with at least one band of rows_per_wave rows before them, or all for
+ * tail_rows = ny -- in bands of
  * tail_rows_per_wave rows whose waves are launched after all the others, so
  * that a launch ends on short waves.  Other tail values give one band height.
  * order as in swe_set_tiling (-1 keeps the current one).  Results do not
@@ -269,7 +272,8 @@ int swe_set_stage_tiling(swe_domain *d, int32_t stage, int32_t rows_per_wave, in
                          int32_t tail_rows, int32_t order);
 
 /* Every tiling swe_autotune_tiling may time for stage kernel `stage` on this
- * domain (the one-height tilings, then the tails tried around each height;
+ * domain (the one-height tilings, then the tails tried around each height,
+ * then the tiling in use and the built-in choice;
  * the tuner also times the winner under the four tile orders, which are not
  * listed), as triples (rows_per_wave, tail_rows_per_wave, tail_rows) in the form of
  * swe_get_stage_tiling, into out[3 * max_tilings] (caller-owned host array;

@@ -196,14 +196,15 @@ inline Tiling make_tiling(int nx, int ny, int by)
 // rows -- at least tail_rows of them -- in bands of by2 < by rows (the tail).
 // The head's tiles are launched first, so the waves that finish the launch
 // are the short tail waves: the drain at the end of a launch shrinks while
-// most rows keep the lower halo overhead of tall bands.  Falls back to one
-// band height when the arguments leave no head or no tail.
+// most rows keep the lower halo overhead of tall bands.  tail_rows = ny puts
+// every row in the tail.  Falls back to one band height when the arguments
+// leave no tail, or less than one head band before it.
 inline Tiling make_tiling_tail(int nx, int ny, int by, int by2, int tail_rows)
 {
     Tiling t = make_tiling(nx, ny, by);
-    if (by2 <= 0 || by2 >= by || tail_rows <= 0 || tail_rows >= ny) return t;
+    if (by2 <= 0 || by2 >= by || tail_rows <= 0 || tail_rows > ny) return t;
     const int nrb1 = (ny - tail_rows) / by;
-    if (nrb1 <= 0) return t;
+    if (nrb1 <= 0 && tail_rows < ny) return t;
     const int ytail = nrb1 * by;
     t.by2 = by2;
     t.nrb1 = nrb1;

@@ -147,7 +147,7 @@ inline Tiling default_tiling(int nx, int ny, int cus, int waves_per_simd)
 // both has one height.
 struct EnsBands {
     int by, by2, tail;
-    Tiling of(int nx, int ny) const { return make_tiling_tail(nx, ny, by, by2, by2 * tail); }
+    Tiling of(int nx, int ny) const { return make_tiling_tail(nx, ny, by, by2, by2 * tail < ny ? by2 * tail : 0); }
 };
 
 constexpr double kEnsembleStart = 1.0;  // rows more than kBandStart: the item and its member's fields
