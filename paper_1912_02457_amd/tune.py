@@ -5,8 +5,9 @@ height one wavefront sweeps; taller tiles amortise the 4-row halo of the
 two-row stencil, shorter ones balance the end of the launch) and the number
 of consecutive work items a wavefront takes.  ``autotune_ensemble`` times a
 few steps of every candidate on the real members and keeps the fastest; the
-result is cached on disk under a key made of the member shapes, so a
-repeated ensemble of the same shapes skips the sweep.
+result is cached on disk under a key made of the member shapes, the kernel
+variant and the candidates, so a repeated ensemble of the same kind skips the
+sweep.
 """
 
 from __future__ import annotations
@@ -21,10 +22,20 @@ DEFAULT_ROWS = (4, 8, 16, 32, 64)
 DEFAULT_CHUNKS = (1, 2, 4)
 
 
-def _key(members, device_name: str) -> str:
+# What the candidates mean: a new number where rows or chunk come to stand for
+# another decomposition, so that entries measured with the old one are not used
+# (1: persistent grid, chunk items per atomic).
+SCHEME = 2
+
+
+def _key(members, device_name: str, rows: Sequence[int], chunks: Sequence[int]) -> str:
+    """Everything the measured choice depends on: the kernel variant (literal
+    projection, state kind, gridded wind), the shapes and the candidates."""
     shapes = sorted((m.nx, m.ny) for m in members)
-    proj = bool(members[0].params.north_projection)
-    h = hashlib.sha1(json.dumps([device_name, proj, shapes]).encode()).hexdigest()
+    p = members[0].params
+    variant = [bool(p.north_projection), bool(p.compensated_state),
+               any(getattr(m, "wind_field", None) is not None for m in members)]
+    h = hashlib.sha1(json.dumps([SCHEME, device_name, variant, shapes, rows, chunks]).encode()).hexdigest()
     return h[:20]
 
 
@@ -57,7 +68,8 @@ def autotune_ensemble(members: Sequence, *, rows: Iterable[int] = DEFAULT_ROWS,
     from .swe import Ensemble
     dev = members[0].device
     name = torch.cuda.get_device_name(dev)
-    key = _key(members, name)
+    rows, chunks = tuple(int(r) for r in rows), tuple(int(c) for c in chunks)
+    key = _key(members, name, rows, chunks)
     table = _load(cache)
     if key in table:
         e = table[key]
