@@ -18,7 +18,7 @@ import os
 import time
 from typing import Iterable, Optional, Sequence, Tuple
 
-DEFAULT_ROWS = (4, 8, 16, 32, 64)
+DEFAULT_ROWS = (4, 8, 16, 32, 64, 0)  # 0: the bands the launch model chooses
 DEFAULT_CHUNKS = (1, 2, 4)
 
 
@@ -61,7 +61,8 @@ def _store(path: Optional[str], table: dict):
 def autotune_ensemble(members: Sequence, *, rows: Iterable[int] = DEFAULT_ROWS,
                       chunks: Iterable[int] = DEFAULT_CHUNKS, steps: int = 32,
                       cache: Optional[str] = None) -> Tuple[int, int, dict]:
-    """Returns (rows_per_wave, chunk, report).  The members' states advance
+    """Returns (rows_per_wave, chunk, report); rows_per_wave may be 0, the
+    library's own choice of bands.  The members' states advance
     by ``steps + 2`` steps per candidate tried (the sweep runs the real
     workload); use fresh or throw-away domains when that matters."""
     import torch

@@ -66,3 +66,8 @@ def test_entries_of_the_earlier_launch_scheme_are_not_used(tuner, tmp_path):
     cached, tried = tuner(cache)
     assert not cached and len(tried) > 1
     assert old in json.loads(cache.read_text())
+
+
+def test_the_built_in_choice_is_a_candidate(tuner, tmp_path):
+    cached, tried = tuner(tmp_path / "tune.json")
+    assert not cached and (0, 1) in tried
