@@ -29,14 +29,23 @@ struct EnsLayout {
     size_t mem, items, ctrl, total;
 };
 
-using Shapes = std::vector<std::pair<int, int>>;
+// (nx, ny) of an ensemble's members
+class Shapes {
+public:
+    Shapes(swe_domain *const *m, int n) : m_(m), n_(n) {}
+    struct Iterator {
+        swe_domain *const *m;
+        std::pair<int, int> operator*() const { return {(*m)->p.nx, (*m)->p.ny}; }
+        Iterator &operator++() { ++m; return *this; }
+        bool operator!=(const Iterator &o) const { return m != o.m; }
+    };
+    Iterator begin() const { return {m_}; }
+    Iterator end() const { return {m_ + n_}; }
 
-Shapes shapes_of(swe_domain *const *m, int n)
-{
-    Shapes s;
-    for (int k = 0; k < n; ++k) s.emplace_back(m[k]->p.nx, m[k]->p.ny);
-    return s;
-}
+private:
+    swe_domain *const *m_;
+    int n_;
+};
 
 // of the current device; the workspace query and the creation must agree
 int device_cus()
@@ -48,7 +57,8 @@ int device_cus()
     return cus;
 }
 
-int64_t count_items(const Shapes &shapes, const EnsBands &b)
+template <class S>
+int64_t count_items(const S &shapes, const EnsBands &b)
 {
     int64_t t = 0;
     for (const auto &sh : shapes) t += b.of(sh.first, sh.second).ntiles;
@@ -182,7 +192,7 @@ int swe_ensemble_workspace_bytes(swe_domain *const *members, int32_t n, int32_t 
     if (!members || n < 1) return set_error(SWE_E_ARG, "an ensemble needs at least one member");
     for (int k = 0; k < n; ++k)
         if (!members[k]) return set_error(SWE_E_ARG, "NULL member");
-    const Shapes shapes = shapes_of(members, n);
+    const Shapes shapes(members, n);
     *bytes = ens_layout(n, count_items(shapes, ensemble_bands(shapes, rows_per_wave, device_cus()))).total;
     return SWE_OK;
 }
@@ -195,7 +205,7 @@ int swe_ensemble_create(swe_domain *const *members, int32_t n, void *dev_workspa
     if (!out || !dev_workspace || rows_per_wave < 0 || rows_per_wave > 4096 || chunk < 0 || chunk > 1024)
         return set_error(SWE_E_ARG, "bad arguments");
     if (((uintptr_t)dev_workspace) % kAlign) return set_error(SWE_E_ARG, "workspace must be 256-byte aligned");
-    const Shapes shapes = shapes_of(members, n);
+    const Shapes shapes(members, n);
     EnsBands bands = ensemble_bands(shapes, rows_per_wave, device_cus());
     int64_t nitems = count_items(shapes, bands);
     if (nitems > (int64_t)1 << 31 || bytes < ens_layout(n, nitems).total) {

@@ -24,7 +24,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <vector>
 
 #include "swe_device.h"
 
@@ -43,16 +42,19 @@ struct CuGroup {
 
 // Time (in rows of one wave) until the last of n1 blocks of c1 rows and then
 // n2 blocks of c2 rows is done, on ncu CUs with room for `room` blocks each.
+// A group of CUs is split where one of the two queues runs out among its CUs,
+// so there are never more than three (and no memory is allocated: this runs
+// inside calls that have no way to report that there is none).
 inline double launch_rows(long n1, double c1, long n2, double c2, int ncu, int room)
 {
     // all but the last eight rounds of tall blocks run in step
     const long round = (long)ncu * room, extra = std::max(0L, n1 / round - 8);
     n1 -= extra * round;
     const double ahead = (double)extra * c1 * (1.0 + kSharing * (room - 1));
-    std::vector<CuGroup> g;
-    g.push_back(CuGroup{ncu, 0, {}, 0.0});
+    CuGroup g[3] = {CuGroup{ncu, 0, {}, 0.0}};
+    int ng = 1;
     // one more block for each CU of group k, split where the queue changes
-    auto give = [&](size_t k) {
+    auto give = [&](int k) {
         while (n1 + n2 > 0) {
             long &left = n1 > 0 ? n1 : n2;
             const double c = n1 > 0 ? c1 : c2;
@@ -66,23 +68,23 @@ inline double launch_rows(long n1, double c1, long n2, double c2, int ncu, int r
             part.w[part.n++] = c;
             g[k].count -= part.count;
             left = 0;
-            g.push_back(part);
+            g[ng++] = part;
         }
     };
     auto pace = [](int n) { return 1.0 / (1.0 + kSharing * (n - 1)); };  // rows per unit of time of each block
     for (int layer = 0; layer < room; ++layer)
-        for (size_t k = 0, m = g.size(); k < m; ++k)
+        for (int k = 0, m = ng; k < m; ++k)
             if (g[k].n == layer) give(k);
     double last = 0.0;
     while (true) {
-        size_t k = g.size();
+        int k = ng;
         double t = INFINITY;
-        for (size_t q = 0; q < g.size(); ++q)
+        for (int q = 0; q < ng; ++q)
             if (g[q].n > 0) {
                 const double e = g[q].since + *std::min_element(g[q].w, g[q].w + g[q].n) / pace(g[q].n);
                 if (e < t) { t = e; k = q; }
             }
-        if (k == g.size()) return ahead + last;
+        if (k == ng) return ahead + last;
         last = t;
         CuGroup &x = g[k];
         const double done = (t - x.since) * pace(x.n);
@@ -92,11 +94,11 @@ inline double launch_rows(long n1, double c1, long n2, double c2, int ncu, int r
         const int freed = x.n - n;
         x.n = n;
         x.since = t;
-        const size_t before = g.size();
+        const int before = ng;
         for (int q = 0; q < freed && n1 + n2 > 0; ++q) {
             give(k);
             // a part split off still waits for its other blocks
-            for (size_t p = before; p < g.size(); ++p)
+            for (int p = before; p < ng; ++p)
                 for (int r = g[p].n - n; r < freed && n1 + n2 > 0 && r <= q; ++r) give(p);
         }
     }
