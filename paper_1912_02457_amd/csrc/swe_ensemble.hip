@@ -21,9 +21,6 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
     } while (0)
 
 constexpr int kEnsGraphChunk = 16;
-// One item per wavefront: the band heights already set how long a wave runs,
-// and several items to a wave leave the last waves with uneven loads.
-constexpr int kDefaultChunk = 1;
 
 struct EnsLayout {
     size_t mem, items, ctrl, total;
@@ -96,7 +93,7 @@ struct swe_ensemble {
     EnsCtrl *d_ctrl = nullptr;
     int64_t nitems = 0;
     int by = 0;
-    int chunk = kDefaultChunk;
+    int chunk = 1;
     int nblocks = 0;
     int parity = 0;
     bool proj = false;
@@ -228,7 +225,7 @@ int swe_ensemble_create(swe_domain *const *members, int32_t n, void *dev_workspa
     e->d_ctrl = (EnsCtrl *)(e->ws + L.ctrl);
     e->nitems = nitems;
     e->by = bands.by;
-    e->chunk = chunk ? chunk : kDefaultChunk;
+    e->chunk = ensemble_chunk(nitems, chunk);
     e->proj = members[0]->p.north_projection != 0;
     e->comp = members[0]->p.compensated_state != 0;
     for (int k = 0; k < n; ++k) e->w10 |= members[k]->dom.w10n > 0;
@@ -249,12 +246,11 @@ int swe_ensemble_create(swe_domain *const *members, int32_t n, void *dev_workspa
     const int64_t heads = (int64_t)items.size();
     for (int k = 0; k < n; ++k)
         for (int t = hm[k].T.ntiles1; t < hm[k].T.ntiles; ++t) items.push_back(EnsItem{k, t});
-    // blocks of four waves, a multiple of the eight XCDs
     const int64_t per_block = (int64_t)kWavesPerBlock * e->chunk;
     EnsCtrl hc{};
     hc.nitems = nitems;
     hc.nblk1 = (int32_t)((heads + per_block - 1) / per_block);
-    e->nblocks = (int)(((nitems + per_block - 1) / per_block + 7) / 8 * 8);
+    e->nblocks = (int)ensemble_blocks(nitems, e->chunk);
     hipStream_t s = e->stream;
     // member streams: everything is ordered on the ensemble stream from now on
     for (auto *m : e->members) {

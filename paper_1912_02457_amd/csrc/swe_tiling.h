@@ -203,4 +203,20 @@ EnsBands ensemble_bands(const Shapes &shapes, int rows_per_wave, int cus)
     return best;
 }
 
+// Items per wavefront and blocks of an ensemble launch: `chunk` items (0: one)
+// -- band heights already set how long a wave runs, and several items to a wave
+// leave the last waves with uneven loads -- or as many more as keep a launch
+// below 2^32 threads, the limit of a grid.
+inline int ensemble_chunk(int64_t items, int chunk)
+{
+    const int64_t waves = ((((int64_t)1 << 32) / (kWavesPerBlock * kWave)) - 16) * kWavesPerBlock;
+    return (int)std::max<int64_t>(chunk ? chunk : 1, (items + waves - 1) / waves);
+}
+// blocks of four waves, a multiple of the eight XCDs
+inline int64_t ensemble_blocks(int64_t items, int chunk)
+{
+    const int64_t per_block = (int64_t)kWavesPerBlock * chunk;
+    return ((items + per_block - 1) / per_block + 7) / 8 * 8;
+}
+
 }  // namespace swe

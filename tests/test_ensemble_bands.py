@@ -71,3 +71,38 @@ def test_ensemble_bands(tmp_path):
                     f"-I{ROCM_INCLUDE}", f"-I{CSRC}", str(src), "-o", exe], check=True, capture_output=True, text=True)
     r = subprocess.run([exe], capture_output=True, text=True, timeout=600)
     assert r.returncode == 0 and "bad 0" in r.stdout, r.stdout[-2000:] + r.stderr[-2000:]
+
+
+GRID = r"""
+#include "swe_tiling.h"
+#include <cstdio>
+using namespace swe;
+int main()
+{
+    long bad = 0;
+    const int64_t items[] = {1, 4, 4096, 1 << 20, ((int64_t)1 << 26) - 64, (int64_t)1 << 26, ((int64_t)1 << 27) + 5, (int64_t)1 << 31};
+    for (int64_t n : items) for (int chunk : {0, 1, 3, 64, 1024}) {
+        const int c = ensemble_chunk(n, chunk);
+        const int64_t blocks = ensemble_blocks(n, c);
+        // every item has a wave, blocks come in eights, and a launch has fewer
+        // than 2^32 threads
+        if (c < 1 || blocks * kWavesPerBlock * c < n || blocks % 8 || blocks * kWavesPerBlock * kWave >= ((int64_t)1 << 32)) { ++bad; printf("%lld %d: %d %lld\n", (long long)n, chunk, c, (long long)blocks); }
+        // what is asked for is kept where it can be
+        if (n < ((int64_t)1 << 26) - 64 && c != (chunk ? chunk : 1)) ++bad;
+    }
+    printf("bad %ld\n", bad);
+    return bad != 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir(ROCM_INCLUDE),
+                    reason="needs g++ and the HIP headers")
+def test_ensemble_grid_stays_below_the_launch_limit(tmp_path):
+    src = tmp_path / "grid.cpp"
+    src.write_text(GRID)
+    exe = str(tmp_path / "grid")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-fsanitize=address,undefined", "-D__HIP_PLATFORM_AMD__",
+                    f"-I{ROCM_INCLUDE}", f"-I{CSRC}", str(src), "-o", exe], check=True, capture_output=True, text=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0 and "bad 0" in r.stdout, r.stdout[-2000:] + r.stderr[-2000:]
