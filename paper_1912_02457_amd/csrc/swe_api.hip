@@ -540,10 +540,9 @@ int swe_init_domain(const swe_params *p, void *dev_workspace, size_t bytes, void
         if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         d->cus = cus > 0 ? cus : 256;
     }
-    for (int st = 0; st < 2; ++st) {
+    for (int st = 0; st < 2; ++st)
         d->wps[st] = stage_waves_per_simd(st + 1, p->north_projection != 0, p->compensated_state != 0);
-        d->T[st] = default_tiling(nx, ny, d->cus, d->wps[st]);
-    }
+    default_tilings(nx, ny, d->cus, d->wps, d->T);
 
     hipStream_t s = d->stream;
     int r = SWE_OK;
@@ -931,9 +930,9 @@ int swe_set_tiling(swe_domain *d, int32_t rows_per_wave, int32_t order)
     if (d->ensemble) return fail(SWE_E_STATE, "domain belongs to an ensemble");
     if (rows_per_wave < 0 || rows_per_wave > 4096) return fail(SWE_E_ARG, "rows_per_wave out of range");
     if (order < -1 || order > 3) return fail(SWE_E_ARG, "order must be -1 (default) or 0..3");
+    if (!rows_per_wave) default_tilings(d->p.nx, d->p.ny, d->cus, d->wps, d->T);
     for (int st = 0; st < 2; ++st) {
-        d->T[st] = rows_per_wave ? make_tiling(d->p.nx, d->p.ny, rows_per_wave)
-                                 : default_tiling(d->p.nx, d->p.ny, d->cus, d->wps[st]);
+        if (rows_per_wave) d->T[st] = make_tiling(d->p.nx, d->p.ny, rows_per_wave);
         if (order >= 0) d->T[st].order = order;
     }
     drop_graphs(d);

@@ -143,6 +143,15 @@ inline Tiling default_tiling(int nx, int ny, int cus, int waves_per_simd)
     return best;
 }
 
+// Both stages' tilings: chosen once where the same number of waves of both fit
+// (creating a domain of 2600 x 900 takes 3.6 ms, a choice 0.06 of
+// it).
+inline void default_tilings(int nx, int ny, int cus, const int *waves_per_simd, Tiling *out)
+{
+    out[0] = default_tiling(nx, ny, cus, waves_per_simd[0]);
+    out[1] = waves_per_simd[1] == waves_per_simd[0] ? out[0] : default_tiling(nx, ny, cus, waves_per_simd[1]);
+}
+
 // The bands of an ensemble's members: `by` rows, and after them, where tail is
 // not 0, bands of by2 rows: at least `tail` of them in each member, and the
 // rows that whole bands of `by` leave before those.  A member too short for

@@ -86,6 +86,16 @@ int main()
         const double c1 = 2.5 + r() % 15, c2 = 2.5 + r() % 4;
         check(r() % 2000, std::max(c1, c2), r() % 2000, std::min(c1, c2), 1 + r() % 40, 1 + r() % 8);
     }
+    // both stages at once: each what it would be alone
+    for (int w1 = 1; w1 <= 8; ++w1) for (int w2 = 1; w2 <= 8; ++w2) for (int nx : {61, 777, 2600}) {
+        const int w[2] = {w1, w2};
+        Tiling T[2];
+        default_tilings(nx, 333, 256, w, T);
+        for (int q = 0; q < 2; ++q) {
+            const Tiling U = default_tiling(nx, 333, 256, w[q]);
+            bad += T[q].by != U.by || T[q].by2 != U.by2 || T[q].nrb1 != U.nrb1 || T[q].nblocks != U.nblocks || T[q].order != U.order;
+        }
+    }
     const std::pair<int, int> one[] = {{777, 333}}, many[] = {{2600, 900}, {61, 1}, {300, 200}, {1000, 600}};
     const long before = allocations;
     for (int w = 1; w <= 8; ++w) for (int nx : {2, 128, 2600, 30000}) bad += default_tiling(nx, 900, 256, w).by < 1;
