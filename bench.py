@@ -8,7 +8,7 @@ with the time step computed on the device from the CFL condition.  Inputs are
 resident in HBM before the timed region starts.  Prints ONE JSON line; beside
 the headline figure it carries
   "ensemble": 256 coastal members (200..1000 x 200..600 cells) advanced by
-              the persistent ensemble launch, against a per-domain loop;
+              the ensemble launch, against a per-domain loop;
   "serving":  the continuous-batching server on Poisson arrivals of forecast
               requests (time-scaled: horizons and inter-arrival times x0.1),
               with p50/p99 latency next to throughput;
@@ -72,7 +72,7 @@ def parse():
     ap.add_argument("--serve-max-active", type=int, default=128)
     ap.add_argument("--serve-steps-per-tick", type=int, default=24)
     ap.add_argument("--serve-rows", type=int, default=0, help="rows per tile of the server's ensemble (0 = default)")
-    ap.add_argument("--serve-chunk", type=int, default=0, help="tiles per queue pop of the server's ensemble (0 = default)")
+    ap.add_argument("--serve-chunk", type=int, default=0, help="work items per wavefront of the server's ensemble (0 = default)")
     ap.add_argument("--serve-unloaded-requests", type=int, default=150,
                     help="requests of the unloaded stream (0 = skip it)")
     ap.add_argument("--serve-unloaded-spread", type=float, default=8.0,
@@ -674,7 +674,7 @@ def _ensemble_leg(wls, comp, S, torch):
 
 def bench_ensemble(a, torch):
     """256-member ensemble (coastal 1 km domains, walls, per-member wind),
-    each member with its own dt: aggregate cell-updates/s of the persistent
+    each member with its own dt: aggregate cell-updates/s of the
     ensemble launch (autotuned tiles, graph replay) against stepping the same
     domains one after the other, for the float32 state (inside the parity
     bar over the 500 steps: members 0-7 are compared with the oracle) and

@@ -6,7 +6,8 @@
 // block of rows with a sliding register window.  Neighbours along x come from
 // the adjacent lanes (cross-lane shuffles), neighbours along y from the rows
 // kept in registers, so every face flux is evaluated once and reused by the
-// two cells that share the face, and no LDS is needed.  Global loads are
+// two cells that share the face.  LDS holds only the boundary state of a
+// tile's relaxation zones (FrsTable, 3.2 KB a wave).  Global loads are
 // 64-float (256 B) row segments.  Ghost cells sit in a 2-cell frame around
 // every plane, written by the stage that produces the state (swe_device.h).
 //

@@ -144,8 +144,7 @@ inline Tiling default_tiling(int nx, int ny, int cus, int waves_per_simd)
 }
 
 // Both stages' tilings: chosen once where the same number of waves of both fit
-// (creating a domain of 2600 x 900 takes 3.6 ms, a choice 0.06 of
-// it).
+// (creating a 2600 x 900 domain takes 3600 us, a choice 60 of them).
 inline void default_tilings(int nx, int ny, int cus, const int *waves_per_simd, Tiling *out)
 {
     out[0] = default_tiling(nx, ny, cus, waves_per_simd[0]);
