@@ -407,7 +407,8 @@ typedef struct swe_server_stats {
 } swe_server_stats;
 
 /* dev_arena: caller-owned device memory (256-byte aligned) from which every
- * admitted request's workspace and the ensemble's queue are carved.  Work
+ * admitted request's workspace and the ensemble's queue are carved (and, at
+ * its end and only until a request needs the room, a longer queue).  Work
  * runs on hip_stream; uploads of joining requests on upload_stream (may be
  * the same), overlapping the running tick.  max_active >= 1;
  * steps_per_tick >= 1; rows_per_wave / chunk as for the ensemble (0 =

@@ -11,15 +11,17 @@
 // 2.25 blocks per CU are as slow as three, and a tail of short bands evens out
 // what the tall ones leave.
 //
-// The two constants and kOneHeight are fitted to event times of both stages,
+// The two constants and kOneHeight were fitted to event times of both stages,
 // both state kinds, about 50 tilings of each of 15 domains from 128 x 128 to
-// 4096 x 4096 (100 x 4000 and 4000 x 100 among them): the tiling chosen is on
-// average 1.4 % slower than the best one measured, at worst 9 %.  A step in us
-// with the rule before it (work spread over the wave slots plus one wave's
-// chain, one band height, strip-major tiles) and with this one: 128 x 128
-// 13.3 and 9.6, 512 x 512 18.9 and 14.5, 1024 x 1024 beach 45 and 39, 2600 x
-// 900 coast 72 and 61 (float32 state 63 and 53), 2048 x 2048 130 and 86, 4096
-// x 4096 590 and 415.
+// 4096 x 4096 (100 x 4000 and 4000 x 100 among them).  With the present kernels
+// a launch at the tiling chosen takes on average 3 % longer than at the best
+// one measured for it, at worst 15 % (2048 x 2048, stage 1); with gridded wind
+// and the literal projection, which were not in the fit, 2 and 3 % and 9 %.
+// A step in us with the rule before it (work spread over the wave slots plus
+// one wave's chain, one band height, strip-major tiles) and with this one: 128
+// x 128 13.3 and 9.1, 512 x 512 18.9 and 14.2, 1024 x 1024 beach 45 and 38,
+// 2600 x 900 coast 72 and 57 (float32 state 63 and 50), 2048 x 2048 130 and
+// 91, 4096 x 4096 590 and 420.
 #pragma once
 
 #include <algorithm>
